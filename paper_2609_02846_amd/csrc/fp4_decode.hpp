@@ -38,6 +38,14 @@ __device__ __forceinline__ void decode8(uint32_t x, const uint2& t, uint32_t* ou
     out[3] = __builtin_bit_cast(uint32_t, v3);
 }
 
+// Two floats to two bf16 (round to nearest even), packed low-first.
+__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
+    typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+    const f32x2_t v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+
 // One thread's share of a K-slice: one row of 64 k-elements (4 blocks).
 // Loads go straight into these registers and nothing consumes them until the
 // decode one iteration later, so no wait is placed between issue and the

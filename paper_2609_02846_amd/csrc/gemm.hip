@@ -326,14 +326,6 @@ __device__ __forceinline__ void mfma16_t(f32x16_t (&acc)[4][4], const Frags& f) 
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.b[j], f.a[i], acc[i][j], 0, 0, 0);
 }
 
-// Two floats to two bf16 (round to nearest even), packed low-first.
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
-    typedef __attribute__((ext_vector_type(2))) float f32x2_t;
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
-    const f32x2_t v = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
-
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 typedef __attribute__((address_space(1))) void* glb_void_ptr;
 
@@ -1684,6 +1676,8 @@ hipError_t launch_gemm(BScale bmode, float amul, int64_t M, int64_t N, int64_t K
                        const uint8_t* b_scales, const float* b_dec, void* c, bool c_bf16,
                        hipStream_t s, const FixedScratch* fx) {
     if (M == 0 || N == 0) return hipSuccess;
+    if (skinny_gemm(M, N, K))
+        return launch_gemm_skinny(bmode, amul, M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16, s);
     switch (bmode) {
         case BScale::Row:
             return launch_mode<(int)BScale::Row>(M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16, amul, s,
