@@ -11,16 +11,20 @@
 // one scale byte per 16 k-elements; the B scales are per row (wgrad) or per
 // 16x16 weight tile (fprop, and dgrad on the transposed weight).
 //
-// Kernels (gfx950, one 256-thread workgroup per CU, 256 x 256 output tiles,
-// four waves of 128 x 128 in a 2 x 2 grid, 16 v_mfma_f32_32x32x16_f16
-// accumulators per wave = all 256 AccVGPRs):
+// Kernels of this file (gfx950, one 256-thread workgroup per CU, 256 x 256
+// output tiles, four waves of 128 x 128 in a 2 x 2 grid, 16
+// v_mfma_f32_32x32x16_f16 accumulators per wave = all 256 AccVGPRs):
 //  * K % 256 == 0, operands and C below 2^31 bytes: gemm_fp4_reg_kernel,
 //    persistent; packed FP4 rows and scale codes staged in LDS by direct
 //    loads four 64-k slices at a time, each wave decoding its own fragments
 //    in registers (no fp16 copy through LDS);
-//  * K % 64 == 0: gemm_fp4_dma_kernel, packed slices staged by direct loads
-//    and decoded once per workgroup into a double-buffered fp16 LDS stage;
-//  * any K % 16 == 0: gemm_fp4_kernel, the same with register-staged loads.
+//  * operands of 2^31 bytes and more (64-bit addresses): gemm_fp4_dma_kernel
+//    for K % 64 == 0, packed slices staged by direct loads and decoded once
+//    per workgroup into a double-buffered fp16 LDS stage, and
+//    gemm_fp4_kernel for any K % 16 == 0, the same with register-staged
+//    loads (it also writes the zeros of K = 0).
+// Few output rows run in gemm_skinny.hip; calls that fill the chip better in
+// smaller tiles, and every other K, in gemm_mid.hip (launch_mode).
 // Decoding writes each UE5M3 scale s as mu * 2^E (mu = 1 + m/8 in [1, 2), or
 // 0 for code 0) or reads the code as an fp16 bit pattern (c << 7 is its
 // value).  The gfx950 FP4 -> FP16 conversion applies a power-of-two scale
@@ -32,6 +36,7 @@
 // share A and B slices in that XCD's L2.
 #include "codec.hpp"
 #include "fp4_decode.hpp"
+#include "gemm_regs.hpp"
 #include "launch.hpp"
 
 #include <atomic>
@@ -74,9 +79,6 @@ __device__ __forceinline__ void load_frags(Frags& f, const uint16_t* __restrict_
         f.b[j] = __builtin_bit_cast(f16x8_t, u32x4_t{v.x, v.y, v.z, v.w});
     }
 }
-
-// Instruction classes for the scheduling-group builtins.
-constexpr int kSgValu = 0x002, kSgMfma = 0x008, kSgVmemRead = 0x020, kSgDsRead = 0x100;
 
 // The 16 MFMAs of one k-step; with DEC, the four decode blocks of one operand
 // row of the next slice (r -> dst) are interleaved with them.
@@ -253,8 +255,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_kernel(
 }
 
 // ===================================================================== //
-// K % 64 == 0 path: packed operands staged in LDS by direct global->LDS  //
-// loads, one slice ahead, so that no register holds in-flight data.      //
+// Large operands, K % 64 == 0: packed operands staged in LDS by direct     //
+// loads, one slice ahead, so that no register holds in-flight data.       //
 // ===================================================================== //
 //
 // LDS (160 KB, the gfx950 maximum):
@@ -325,9 +327,6 @@ __device__ __forceinline__ void mfma16_t(f32x16_t (&acc)[4][4], const Frags& f) 
         for (int j = 0; j < 4; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.b[j], f.a[i], acc[i][j], 0, 0, 0);
 }
-
-typedef __attribute__((address_space(3))) void* lds_void_ptr;
-typedef __attribute__((address_space(1))) void* glb_void_ptr;
 
 // Direct global->LDS loads of one slice: each wave moves 64 A rows and 64 B
 // rows (4 instructions of 64 lanes x 16 B).  Lane l of instruction i covers
@@ -574,10 +573,6 @@ struct RegSlice {
     uint32_t s[8];
 };
 
-__device__ __forceinline__ uint32_t half_scales(uint32_t word, uint32_t sel) {
-    return __builtin_amdgcn_perm(0u, word, sel) << 7;
-}
-
 // Slice SL of the stage (P, S) into R.  pa / pb: byte offsets of the lane's
 // first A / B stage row (group 0); xo: the lane's chunk offset for this slice.
 template <int SL>
@@ -594,17 +589,6 @@ __device__ __forceinline__ void read_sup_slice(RegSlice& R, const uint8_t* P, co
         const int srow_off = ((g < 4 ? pa : pb) / kSupRowBytes + (g & 3) * 32) * (kSupK * 4);
         R.s[g] = *reinterpret_cast<const uint32_t*>(S + srow_off + SL * 4);
     }
-}
-
-template <int HSEL>
-__device__ __forceinline__ f16x8_t decode_frag(uint32_t w, uint32_t s2) {
-    const f16x2_t sp = __builtin_bit_cast(f16x2_t, s2);
-    const f16x2_t sc = __builtin_shufflevector(sp, sp, HSEL, HSEL);   // op_sel picks the half
-    const f16x2_t v0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 0.125f, 0) * sc;
-    const f16x2_t v1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 0.125f, 1) * sc;
-    const f16x2_t v2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 0.125f, 2) * sc;
-    const f16x2_t v3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 0.125f, 3) * sc;
-    return f16x8_t{v0[0], v0[1], v1[0], v1[1], v2[0], v2[1], v3[0], v3[1]};
 }
 
 // k-step KK of a slice into MFMA fragments.  At KK = 0 the raw scale words
@@ -626,53 +610,6 @@ __device__ __forceinline__ void decode_kstep(Frags& f, RegSlice& R, uint32_t sel
     for (int i = 0; i < 4; ++i) f.a[i] = decode_frag<KK / 2>(R.w[i][KK], R.s[i]);
 #pragma unroll
     for (int j = 0; j < 4; ++j) f.b[j] = decode_frag<KK / 2>(R.w[4 + j][KK], R.s[4 + j]);
-}
-
-// Direct global->LDS loads written as instructions the compiler does not
-// model: it would otherwise wait for every outstanding direct load before any
-// LDS read (it cannot tell the stage arrays apart), which would remove the
-// overlap.  The kernel counts them itself with vmcnt.  The LDS destination of
-// lane l is m0 + 16 l.
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-    return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_ptr)p);
-}
-
-// Calls f(integral_constant<int, i>) for i in [I0, I1).
-template <int I0, int I1, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (I0 < I1) {
-        f(std::integral_constant<int, I0>{});
-        static_for<I0 + 1, I1>(f);
-    }
-}
-
-// Buffer resource of a raw byte range [base, base + bytes): loads whose
-// per-lane offset falls outside it are dropped by the hardware.
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ i32x4_t buffer_rsrc(const void* base, uint32_t bytes) {
-    const uint64_t a = (uint64_t)(uintptr_t)base;
-    i32x4_t r;
-    r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-    r[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));   // stride 0
-    r[2] = (int)bytes;
-    r[3] = 0x00020000;                                                   // 32-bit data format
-    return r;
-}
-
-// 16 bytes per lane from rsrc at voff + soff into LDS at lds + OFF + 16 lane
-// (the LDS offset is added inside the instruction sequence so that the
-// compiler does not keep one register per destination).
-template <int OFF>
-__device__ __forceinline__ void dma_buf_x4(i32x4_t rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-    asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-                 :: "v"(voff), "s"(rsrc), "s"(soff), "s"(lds), "i"(OFF) : "memory", "m0", "scc");
-}
-
-// vmcnt(n) with expcnt and lgkmcnt left at their maxima (n < 64).
-template <int n>
-__device__ __forceinline__ void wait_vmem() {
-    static_assert(n >= 0 && n < 64, "vmcnt range");
-    __builtin_amdgcn_s_waitcnt((n & 15) | ((n >> 4) << 14) | 0x0F70);
 }
 
 // Per-lane source of a wave's stage loads for one output tile: byte offsets
@@ -763,16 +700,6 @@ __device__ __forceinline__ WorkItem work_item(int it, const SplitPlan& sp, int N
 
 // LDS bytes per wave for the epilogue's row transposition (32 rows x 128 B).
 constexpr int kEpiBytes = 4096;
-
-// Orders a wave's LDS writes before its own later LDS reads of what other
-// lanes wrote (and those reads before the next writes): the LDS serves one
-// wave's instructions in order, so the compiler only must not move memory
-// accesses across this point and the data must have landed.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0)
-    asm volatile("" ::: "memory");
-}
-
 
 // Epilogue of one work item.  Element e of accumulator (i, j) is row
 // 32i + l%32, column 32j + 8(e/4) + 4(l/32) + e%4 of the wave's 128 x 128
@@ -1653,13 +1580,50 @@ hipError_t launch_one(int64_t M, int64_t N, int64_t K, const uint8_t* a, const u
     return hipGetLastError();
 }
 
+// Compute units of the current device.
+hipError_t device_cus(int* cus) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess && *cus <= 0) e = hipErrorInvalidDevice;
+    return e;
+}
+
+// Modelled time (us) of the 256 x 256-tile kernel, for the choice between it
+// and the smaller tiles: whole rounds of one tile per CU plus a last one
+// that is split where launch_reg splits it, each with a fixed part (pipeline
+// fill, epilogue) and tau ns per k, which grows with the share of CUs at
+// work (the clock falls under load).  Model / measured (256 CUs, us): 2000 x
+// 6144 x 4096 (192 tiles) 87 / 84, where the small tiles model 93 and take
+// 95; 4096 x 4096 x 4096 (256) 100 / 102, small 122 / 125; 2000 x 4096 x
+// 6144 (128) 107 / 109, small 91 / 97; 777 x 4096 x 21504 (64) 357 / 352,
+// small 153 / 151.
+double reg_time(int64_t M, int64_t N, int64_t K, int cus) {
+    const int64_t T = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
+    const int64_t full = T / cus, rem = T % cus;
+    const double share = T >= cus ? 1.0 : (double)rem / cus;
+    const double round = 4.0 + 1e-3 * K * (16.3 + (share > 0.5 ? 13.0 * (share - 0.5) : 0.0));
+    double t = 3.0 + full * round;
+    if (rem > 0) t += (full > 0 && rem <= cus / kSplitRemDiv) ? round * rem / cus + 15.0 : round;
+    return t;
+}
+
 template <int BMODE>
 hipError_t launch_mode(int64_t M, int64_t N, int64_t K, const uint8_t* a, const uint8_t* as,
                        const float* ad, const uint8_t* b, const uint8_t* bs, const float* bd,
                        void* c, bool c_bf16, float amul, hipStream_t s, const FixedScratch* fx) {
-    // the register-decode kernel addresses operands and C with 32-bit offsets
+    // the register-decode kernels address operands (and, in 256 x 256 tiles,
+    // C) with 32-bit offsets
     const int64_t kLim = (int64_t)1 << 31;
-    if (K % (4 * BK) == 0 && K > 0 && M * (K / 2) < kLim && N * (K / 2) < kLim && M * N * 4 < kLim)
+    const bool reg = K % (4 * BK) == 0 && K > 0 && M * (K / 2) < kLim && N * (K / 2) < kLim && M * N * 4 < kLim;
+    if (mid_gemm_fits(M, N, K)) {
+        int cus = 0;
+        const hipError_t e = device_cus(&cus);
+        if (e != hipSuccess) return e;
+        if (!reg || mid_gemm_time(M, N, K, cus) < reg_time(M, N, K, cus))
+            return launch_gemm_mid((BScale)BMODE, amul, M, N, K, cus, a, as, ad, b, bs, bd, c, c_bf16, s);
+    }
+    if (reg)
         return c_bf16 ? launch_reg<BMODE, true>(M, N, K, a, as, ad, b, bs, bd, c, amul, s, fx)
                       : launch_reg<BMODE, false>(M, N, K, a, as, ad, b, bs, bd, c, amul, s, fx);
     if (K % BK == 0 && K > 0)

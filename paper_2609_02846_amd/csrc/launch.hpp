@@ -93,6 +93,15 @@ hipError_t launch_gemm_skinny(BScale bmode, float amul, int64_t M, int64_t N, in
                               const uint8_t* a_scales, const float* a_dec, const uint8_t* b,
                               const uint8_t* b_scales, const float* b_dec, void* c, bool c_bf16, hipStream_t s);
 
+// The same GEMM in tiles of 64 or 128 rows and columns: any K % 16 == 0,
+// operands below 2^31 bytes, no workspace.  mid_gemm_time: its modelled time
+// in us on a device of `cus` compute units.
+bool mid_gemm_fits(int64_t M, int64_t N, int64_t K);
+double mid_gemm_time(int64_t M, int64_t N, int64_t K, int cus);
+hipError_t launch_gemm_mid(BScale bmode, float amul, int64_t M, int64_t N, int64_t K, int cus, const uint8_t* a,
+                           const uint8_t* a_scales, const float* a_dec, const uint8_t* b, const uint8_t* b_scales,
+                           const float* b_dec, void* c, bool c_bf16, hipStream_t s);
+
 // The allocation-free GEMM's scratch array on the current device: its
 // device address (taken once per device) and capacity in floats.
 hipError_t noalloc_scratch(FixedScratch* out);
