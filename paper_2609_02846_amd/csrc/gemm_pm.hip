@@ -17,26 +17,37 @@
 //    core's result is exact whenever the exact value is representable;
 //    inexact sums are not rounded to nearest by it, which is why a group is
 //    never accumulated inside the matrix core);
-//  * each workgroup takes, per group, the largest scale-exponent span (the
-//    largest minus the smallest LSB exponent of a row's nonzero blocks) over
-//    its A rows, sA, and over its B rows, sB.  Block j's sum is N_j 2^E_j with
-//    |N_j| <= 16 x (12 x 15)^2 < 2^19 and E_j = La_j + Lb_j - 8, so the
-//    exponents of an output's nonzero block sums lie within sA + sB of each
-//    other;
-//  * sA + sB <= 4: the pairs s_0 + s_1 and s_2 + s_3 are exact in binary32
-//    (|N| 2^d + |N'| < 2^19 (2^4 + 1) < 2^24), so p_j is one RNE binary32
-//    add of the two exact pair sums;
-//  * otherwise, with sA, sB <= 16: the four block sums are added in binary64,
-//    exactly (their bits span at most 2 x 16 + 19 + 2 <= 53 positions), and
-//    p_j is the binary32 RNE conversion of that sum;
-//  * sA or sB > 16: an exact 128-bit integer sum, rounded once;
-//  * c + p_j toward zero: one v_add_f32 with the single-precision round mode
-//    set to toward-zero around the adds (the mode is restored before any
+//  * each workgroup takes, per group, the largest scale-exponent distance
+//    inside a block pair, (0, 1) or (2, 3), over its A rows, sA, and over its
+//    B rows, sB, and whether any row's blocks span more than 16 binades.
+//    Block j's sum is N_j 2^E_j with |N_j| <= 16 x (12 x 15)^2 < 2^19 and
+//    E_j = La_j + Lb_j - 8, so the exponents of the two blocks of a pair lie
+//    within sA + sB of each other;
+//  * sA + sB <= 4: the pair sums s_0 + s_1 and s_2 + s_3 are exact in binary32
+//    (|N| 2^d + |N'| < 2^19 (2^4 + 1) < 2^24 units of the lower exponent), so
+//    the second block's MFMA takes the first one's sum as its accumulator and
+//    still returns the exact value, and p_j is one RNE binary32 add of the
+//    two pair sums;
+//  * otherwise, with no row above 16 binades: the four block sums are added in
+//    binary64, exactly (their bits span at most 2 x 16 + 19 + 2 <= 53
+//    positions), and p_j is the binary32 RNE conversion of that sum;
+//  * otherwise: an exact 128-bit integer sum, rounded once;
+//  * c + p_j toward zero: v_add_f32 with the single-precision round mode set
+//    to toward-zero around 16 adds at a time (the mode is restored before any
 //    other instruction).
 //
+// Bound: VALU, 9 operations per output and group on the binary64 path, 2 on
+// the pair path (the pair sums on the VALU instead of in the MFMA, 4: dgrad
+// 4096 x 4096 x 4096 241 -> 212 us).
+//
 // Tiles: 128 x 128 per 256-thread workgroup (2 per CU), 64 x 64 per wave
-// (2 x 2 accumulators of 32 x 32); operand rows are decoded once per
-// workgroup into a double-buffered LDS stage, one 64-k group ahead.
+// (2 x 2 accumulators of 32 x 32), or 64 x 64 per workgroup (one accumulator
+// per wave) where the large tile would leave CUs without work (launch_pm_t);
+// operand rows are decoded once per workgroup into a double-buffered LDS
+// stage, one 64-k group ahead.  In the small tile a group is a chain of LDS
+// reads, MFMAs, sums and a barrier that few waves hide, so the next group's
+// decode runs between its MFMAs and its sums (1024 x 2048 x 2048: 44 us, with
+// the decode first 53).
 // Groups are processed in ascending k inside one workgroup (no split-K: the
 // toward-zero chain is order dependent).
 #include "codec.hpp"
@@ -46,35 +57,42 @@
 namespace ue5m3 {
 namespace {
 
-constexpr int PM_BM = 128, PM_BN = 128;
 constexpr int PM_LDSK = 64 + 8;                          // padded fp16 row
-constexpr int PM_STAGE = (PM_BM + PM_BN) * PM_LDSK;      // fp16 per stage
 constexpr int PM_THREADS = 256;
 constexpr int PM_XCDS = 8;
 
-// c[i] = c[i] + p[i] rounded toward zero, i = 0..7, with the hardware round
+// c[i] = c[i] + p[i] rounded toward zero, i = 0..15, with the hardware round
 // mode: the single-precision rounding field of MODE (bits 1:0) is set to
-// toward-zero (3) around the eight adds and back to nearest-even (0) after
-// them, all inside one asm statement so that no compiler-placed
-// instruction runs in between.  Wait states after each mode write let the
-// following instructions see it; instructions issued before it keep the mode
-// they were issued with.
-__device__ __forceinline__ void add_rtz8(float* c, const float* p) {
+// toward-zero (3) around the adds and back to nearest-even (0) after them, all
+// inside one asm statement so that no compiler-placed instruction runs in
+// between.  Wait states after each mode write let the following instructions
+// see it; instructions issued before it keep the mode they were issued with.
+__device__ __forceinline__ void add_rtz16(float* c, const float* p) {
     asm volatile(
         "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 3\n\t"
         "s_nop 2\n\t"
-        "v_add_f32 %0, %0, %8\n\t"
-        "v_add_f32 %1, %1, %9\n\t"
-        "v_add_f32 %2, %2, %10\n\t"
-        "v_add_f32 %3, %3, %11\n\t"
-        "v_add_f32 %4, %4, %12\n\t"
-        "v_add_f32 %5, %5, %13\n\t"
-        "v_add_f32 %6, %6, %14\n\t"
-        "v_add_f32 %7, %7, %15\n\t"
+        "v_add_f32 %0, %0, %16\n\t"
+        "v_add_f32 %1, %1, %17\n\t"
+        "v_add_f32 %2, %2, %18\n\t"
+        "v_add_f32 %3, %3, %19\n\t"
+        "v_add_f32 %4, %4, %20\n\t"
+        "v_add_f32 %5, %5, %21\n\t"
+        "v_add_f32 %6, %6, %22\n\t"
+        "v_add_f32 %7, %7, %23\n\t"
+        "v_add_f32 %8, %8, %24\n\t"
+        "v_add_f32 %9, %9, %25\n\t"
+        "v_add_f32 %10, %10, %26\n\t"
+        "v_add_f32 %11, %11, %27\n\t"
+        "v_add_f32 %12, %12, %28\n\t"
+        "v_add_f32 %13, %13, %29\n\t"
+        "v_add_f32 %14, %14, %30\n\t"
+        "v_add_f32 %15, %15, %31\n\t"
         "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 0\n\t"
         "s_nop 2"
-        : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]), "+v"(c[4]), "+v"(c[5]), "+v"(c[6]), "+v"(c[7])
-        : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5]), "v"(p[6]), "v"(p[7]));
+        : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]), "+v"(c[4]), "+v"(c[5]), "+v"(c[6]), "+v"(c[7]),
+          "+v"(c[8]), "+v"(c[9]), "+v"(c[10]), "+v"(c[11]), "+v"(c[12]), "+v"(c[13]), "+v"(c[14]), "+v"(c[15])
+        : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5]), "v"(p[6]), "v"(p[7]), "v"(p[8]),
+          "v"(p[9]), "v"(p[10]), "v"(p[11]), "v"(p[12]), "v"(p[13]), "v"(p[14]), "v"(p[15]));
 }
 
 // Binary32 RNE of the exact sum of four binary32 values (normal or zero),
@@ -128,37 +146,79 @@ __host__ __device__ __noinline__ float rne32_sum4_exact(float b0, float b1, floa
     return neg ? -r : r;
 }
 
-// Span of one operand row's group: the largest minus the smallest scale LSB
-// exponent over its nonzero blocks (nvalid of them), 0 when none is
-// nonzero.  Scale s = i * 2^L with L = e - 18 (exponent field e >= 1,
-// i = 8 + m) or L = -17 (e = 0, i = m).
-__device__ __forceinline__ int span_row(const RowSlice& r, int nvalid) {
-    int lo = 1 << 10, hi = -(1 << 10);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t code = r.code[j] & 0xFFu;
-        const bool nz = j < nvalid && code != 0u && ((r.w[2 * j] | r.w[2 * j + 1]) & 0x77777777u) != 0u;
-        const int e = (int)(code >> 3);
-        const int L = e ? e - 18 : -17;
-        lo = nz ? min(lo, L) : lo;
-        hi = nz ? max(hi, L) : hi;
-    }
-    return hi >= lo ? hi - lo : 0;
-}
-
-// span_row for a group of four whole blocks from the packed codes alone (one
-// code per byte of c4).  It leaves out only code-0 blocks, not blocks whose
-// nibbles are all zero, so it is never below span_row (a wider span only
-// sends a group to a slower exact path).  Scale exponents L + 18 = max(e, 1)
-// rise with the code, so the span is that of the largest code and the
-// smallest nonzero one.
+// What one operand row's group says about the exact paths, from its four
+// packed codes (one code per byte of c4; blocks past K have code 0): the
+// larger of the scale-exponent distances inside its block pairs (0, 1) and
+// (2, 3), or kWideSpan when all its blocks together span more than 16
+// binades.  Scale s = i * 2^L with L = e - 18 (exponent field e >= 1, i = 8 + m)
+// or L = -17 (e = 0, i = m); code-0 blocks sum to zero and are left out, blocks
+// whose nibbles are all zero are not (which can only send a group to a slower
+// exact path).  L + 18 = max(e, 1) rises with the code, so the whole span is
+// that of the largest code and the smallest nonzero one.
+constexpr int kWideSpan = 64;
 __device__ __forceinline__ int span_codes(uint32_t c4) {
     const uint32_t b0 = c4 & 0xFFu, b1 = (c4 >> 8) & 0xFFu, b2 = (c4 >> 16) & 0xFFu, b3 = c4 >> 24;
-    const uint32_t top = max(max(b0, b1), max(b2, b3));
+    auto expo = [](uint32_t b) { return max((int)(b >> 3), 1); };
     // code - 1 wraps code 0 to the largest value: the minimum of these plus
     // one is the smallest nonzero code (0 when every code is 0)
-    const uint32_t low = min(min(b0 - 1u, b1 - 1u), min(b2 - 1u, b3 - 1u)) + 1u;
-    return max((int)(top >> 3), 1) - max((int)(low >> 3), 1);
+    const uint32_t hi01 = max(b0, b1), lo01 = min(b0 - 1u, b1 - 1u);
+    const uint32_t hi23 = max(b2, b3), lo23 = min(b2 - 1u, b3 - 1u);
+    const int p01 = expo(hi01) - expo(lo01 + 1u), p23 = expo(hi23) - expo(lo23 + 1u);
+    const int all = expo(max(hi01, hi23)) - expo(min(lo01, lo23) + 1u);
+    return all > 16 ? kWideSpan : max(p01, p23);
+}
+
+// One thread's share of a group of an operand row: NB of its four 16-element
+// blocks (from block b0) and all four scale codes.
+template <int NB>
+struct PmLoad {
+    uint32_t w[2 * NB];
+    uint32_t c4;
+};
+
+// FULLK: K % 64 == 0, so the group has four whole blocks, the payload pieces
+// are 16-byte aligned and the codes one aligned word.  Otherwise blocks at or
+// past K read the last block and take code 0.
+template <int NB, bool FULLK>
+__device__ __forceinline__ void pm_load(PmLoad<NB>& r, const uint8_t* __restrict__ pay,
+                                        const uint8_t* __restrict__ sc, int b0, int64_t kb0, int64_t kbt) {
+    if (FULLK) {
+#pragma unroll
+        for (int h = 0; h < NB / 2; ++h) {
+            const uint4 v = *reinterpret_cast<const uint4*>(pay + (kb0 + b0) * 8 + 16 * h);
+            r.w[4 * h] = v.x; r.w[4 * h + 1] = v.y; r.w[4 * h + 2] = v.z; r.w[4 * h + 3] = v.w;
+        }
+        r.c4 = *reinterpret_cast<const uint32_t*>(sc + kb0);
+    } else {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const uint2 v = *reinterpret_cast<const uint2*>(pay + min(kb0 + b0 + j, kbt - 1) * 8);
+            r.w[2 * j] = v.x;
+            r.w[2 * j + 1] = v.y;
+        }
+        r.c4 = 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t c = sc[min(kb0 + j, kbt - 1)];
+            r.c4 |= (kb0 + j < kbt ? c : 0u) << (8 * j);
+        }
+    }
+}
+
+// Decoded blocks into the row's LDS stage (code 0 decodes to zeros).
+template <int NB>
+__device__ __forceinline__ void pm_store(const PmLoad<NB>& r, int b0, uint16_t* __restrict__ row) {
+    const uint32_t codes = NB == 4 ? r.c4 : r.c4 >> (8 * b0);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        const uint2 t = scale_factors((codes >> (8 * j)) & 0xFFu);
+        uint32_t o[8];
+        decode8(r.w[2 * j], t, o);
+        decode8(r.w[2 * j + 1], t, o + 4);
+        uint4* d = reinterpret_cast<uint4*>(row + 16 * (b0 + j));
+        d[0] = make_uint4(o[0], o[1], o[2], o[3]);
+        d[1] = make_uint4(o[4], o[5], o[6], o[7]);
+    }
 }
 
 // Raise *dst to the largest v of the wave (every lane active: the decode
@@ -173,15 +233,20 @@ __device__ __forceinline__ void wave_raise(unsigned* dst, unsigned v, int lane) 
     if ((lane & 15) == 15) atomicMax(dst, v);
 }
 
-// FULLK: K % 64 == 0, so every group has four whole blocks and a row's four
-// scale codes of a group are one aligned word (cheaper loads and decode).
-template <int BMODE, bool OUT_BF16, bool FULLK>
-__global__ __launch_bounds__(PM_THREADS, 2) void gemm_pm_kernel(
+// TM x TN: 32 x 32 blocks per wave (a 2 x 2 grid of waves: tiles of 64 TM x
+// 64 TN).  FULLK: K % 64 == 0 (cheaper loads).
+template <int BMODE, int TM, int TN, bool OUT_BF16, bool FULLK>
+__global__ __launch_bounds__(PM_THREADS, TM == 1 ? 3 : 2) void gemm_pm_kernel(
     int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n, const uint8_t* __restrict__ A,
     const uint8_t* __restrict__ As, const float* __restrict__ a_dec, const uint8_t* __restrict__ B,
     const uint8_t* __restrict__ Bs, const float* __restrict__ b_dec, void* __restrict__ C, float amul,
     float grid_d, float inv_grid_d) {
-    __shared__ __attribute__((aligned(16))) uint16_t stages[2][PM_STAGE];
+    constexpr int PM_BM = 64 * TM, PM_BN = 64 * TN;
+    constexpr int PM_ROWS = PM_BM + PM_BN;
+    constexpr int NT = PM_THREADS / PM_ROWS;                 // threads per operand row in the decode
+    constexpr int NB = 4 / NT;                               // blocks of the row each of them decodes
+    static_assert(TM == TN && NT >= 1 && NB >= 2, "whole waves decode rows of one operand");
+    __shared__ __attribute__((aligned(16))) uint16_t stages[2][PM_ROWS * PM_LDSK];
     // largest row span of group g over the A rows (wspan[g % 3][0]) and over
     // the B rows ([1]): raised by every wave while it decodes the group,
     // read by all after the next barrier, cleared by thread 0 two groups
@@ -207,121 +272,123 @@ __global__ __launch_bounds__(PM_THREADS, 2) void gemm_pm_kernel(
     const int64_t m0 = (int64_t)(first_m + rr % gm) * PM_BM;
     const int64_t n0 = (int64_t)(rr / gm) * PM_BN;
 
-    // each thread decodes one operand row: A rows 0..127, then B rows 0..127
+    // NT threads decode each operand row: the A rows by the first half of
+    // the workgroup, the B rows by the second
     const int64_t kbt = K / 16;
     const int64_t nk = (K + 63) / 64;
-    const bool is_a = tid < PM_BM;
-    const int row = tid & (PM_BM - 1);
-    RowSrc src;
+    const bool is_a = tid < PM_THREADS / 2;
+    const int row = (tid & (PM_THREADS / 2 - 1)) / NT;
+    const int b0 = (tid % NT) * NB;
+    const uint8_t *pay, *sc;
     if (is_a) {
         const int64_t am = min(m0 + row, M - 1);
-        src.pay = A + am * (kbt * 8);
-        src.sc = As + am * kbt;
+        pay = A + am * (kbt * 8);
+        sc = As + am * kbt;
     } else {
         const int64_t bn = min(n0 + row, N - 1);
-        src.pay = B + bn * (kbt * 8);
-        src.sc = (BMODE == (int)BScale::Row) ? Bs + bn * kbt : Bs + (bn >> 4) * kbt;
+        pay = B + bn * (kbt * 8);
+        sc = Bs + (BMODE == (int)BScale::Row ? bn : (bn >> 4)) * kbt;
     }
-    src.sc_stride = 1;
     const int srow = (is_a ? 0 : PM_BM) + row;
-    auto nvalid = [&](int64_t g) -> int { return (int)min((int64_t)4, kbt - g * 4); };
 
-    float c[2][2][16];
+    float c[TM][TN][16];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) c[i][j][r] = 0.0f;
 
     if (nk > 0) {
         const int64_t last = (nk - 1) * 4;
-        RowSlice rs;
-        load_slice<FULLK, FULLK>(rs, src, 0, kbt);
-        const int nv0 = nvalid(0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) store_block<FULLK, FULLK>(rs, j, j < nv0, &stages[0][srow * PM_LDSK]);
+        PmLoad<NB> rs;
+        pm_load<NB, FULLK>(rs, pay, sc, b0, 0, kbt);
+        pm_store<NB>(rs, b0, &stages[0][srow * PM_LDSK]);
         if (tid < 6) wspan[tid >> 1][tid & 1] = 0u;
         __syncthreads();
-        wave_raise(&wspan[0][is_a ? 0 : 1], (unsigned)(FULLK ? span_codes(rs.code[0]) : span_row(rs, nv0)), lane);
-        load_slice<FULLK, FULLK>(rs, src, min((int64_t)4, last), kbt);
+        wave_raise(&wspan[0][is_a ? 0 : 1], (unsigned)span_codes(rs.c4), lane);
+        pm_load<NB, FULLK>(rs, pay, sc, b0, min((int64_t)4, last), kbt);
         __syncthreads();
-        // the group's path from the two spans (uniform): 0 when the block
-        // pairs add exactly in binary32, 1 when the four block sums add
-        // exactly in binary64, 2 otherwise (exact integer sum)
+        // the group's path from the two sides' largest span_codes (uniform):
+        // 0 when the block pairs add exactly in binary32, 1 when the four
+        // block sums add exactly in binary64, 2 otherwise (exact integer sum)
         auto path_of = [&](int f) {
             const int sa = __builtin_amdgcn_readfirstlane((int)wspan[f][0]);
             const int sb = __builtin_amdgcn_readfirstlane((int)wspan[f][1]);
-            return (sa > 16 || sb > 16) ? 2 : (sa + sb <= 4 ? 0 : 1);
+            return max(sa, sb) >= kWideSpan ? 2 : (sa + sb <= 4 ? 0 : 1);
         };
-        int path = path_of(0);
-        int fnext = 1, fclear = 2;                       // (g + 1) % 3, (g + 2) % 3
-
+        int fcur = 0, fnext = 1, fclear = 2;             // g % 3, (g + 1) % 3, (g + 2) % 3
         for (int64_t g = 0; g < nk; ++g) {
             const uint16_t* cur = stages[g & 1];
             uint16_t* nxt = stages[(g + 1) & 1];
             // decode group g + 1 (its bytes arrived during group g - 1)
-            if (g + 1 < nk) {
-                const int nv = nvalid(g + 1);
+            auto decode_next = [&]() {
+                if (g + 1 < nk) {
+                    pm_store<NB>(rs, b0, nxt + srow * PM_LDSK);
+                    wave_raise(&wspan[fnext][is_a ? 0 : 1], (unsigned)span_codes(rs.c4), lane);
+                    pm_load<NB, FULLK>(rs, pay, sc, b0, min((g + 2) * 4, last), kbt);
+                }
+            };
+            // group g: its fragments, then per 32 x 32 block the MFMAs and sums
+            f16x8_t bf[TN][4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) store_block<FULLK, FULLK>(rs, j, j < nv, nxt + srow * PM_LDSK);
-                wave_raise(&wspan[fnext][is_a ? 0 : 1], (unsigned)(FULLK ? span_codes(rs.code[0]) : span_row(rs, nv)),
-                           lane);
-                load_slice<FULLK, FULLK>(rs, src, min((g + 2) * 4, last), kbt);
-            }
-            // group g: one zero-accumulator MFMA per 16-k block and 32x32 tile
-            f16x8_t bf[2][4];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const uint16_t* lb = cur + (PM_BM + wn * 64 + j * 32 + (lane & 31)) * PM_LDSK + (lane >> 5) * 8;
+            for (int j = 0; j < TN; ++j) {
+                const uint16_t* lb = cur + (PM_BM + wn * 32 * TN + j * 32 + (lane & 31)) * PM_LDSK + (lane >> 5) * 8;
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
                     const uint4 v = *reinterpret_cast<const uint4*>(lb + b * 16);
                     bf[j][b] = __builtin_bit_cast(f16x8_t, v);
                 }
             }
+            const int path = path_of(fcur);
+            if (TM > 1) decode_next();
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
+            for (int i = 0; i < TM; ++i) {
                 f16x8_t af[4];
-                const uint16_t* la = cur + (wm * 64 + i * 32 + (lane & 31)) * PM_LDSK + (lane >> 5) * 8;
+                const uint16_t* la = cur + (wm * 32 * TM + i * 32 + (lane & 31)) * PM_LDSK + (lane >> 5) * 8;
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
                     const uint4 v = *reinterpret_cast<const uint4*>(la + b * 16);
                     af[b] = __builtin_bit_cast(f16x8_t, v);
                 }
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < TN; ++j) {
                     const f32x16_t z = {};
-                    const f32x16_t s0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[0], bf[j][0], z, 0, 0, 0);
-                    const f32x16_t s1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[1], bf[j][1], z, 0, 0, 0);
-                    const f32x16_t s2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[2], bf[j][2], z, 0, 0, 0);
-                    const f32x16_t s3 = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[3], bf[j][3], z, 0, 0, 0);
+                    auto block = [&](int b, const f32x16_t& acc) {
+                        return __builtin_amdgcn_mfma_f32_32x32x16_f16(af[b], bf[j][b], acc, 0, 0, 0);
+                    };
                     float p[16];
                     if (path == 0) {
+                        const f32x16_t s01 = block(1, block(0, z)), s23 = block(3, block(2, z));
+                        if (TM == 1) decode_next();
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) p[r] = (s0[r] + s1[r]) + (s2[r] + s3[r]);
-                    } else if (path == 1) {
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            double sum = (double)s0[r] + (double)s1[r];
-                            sum += (double)s2[r];
-                            sum += (double)s3[r];
-                            p[r] = (float)sum;
-                        }
+                        for (int r = 0; r < 16; ++r) p[r] = s01[r] + s23[r];
                     } else {
+                        const f32x16_t s0 = block(0, z), s1 = block(1, z), s2 = block(2, z), s3 = block(3, z);
+                        if (TM == 1) decode_next();
+                        if (path == 1) {
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) p[r] = rne32_sum4_exact(s0[r], s1[r], s2[r], s3[r]);
+                            for (int r = 0; r < 16; ++r) {
+                                double sum = (double)s0[r] + (double)s1[r];
+                                sum += (double)s2[r];
+                                sum += (double)s3[r];
+                                p[r] = (float)sum;
+                            }
+                        } else {
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) p[r] = rne32_sum4_exact(s0[r], s1[r], s2[r], s3[r]);
+                        }
                     }
-                    add_rtz8(&c[i][j][0], &p[0]);
-                    add_rtz8(&c[i][j][8], &p[8]);
+                    add_rtz16(c[i][j], p);
                 }
             }
             // group g + 1 complete in LDS, group g's stage free; its span flag
             if (tid < 2) wspan[fclear][tid] = 0u;
             __syncthreads();
-            path = path_of(fnext);
+            const int f = fcur;
+            fcur = fnext;
             fnext = fclear;
-            fclear = fclear == 2 ? 0 : fclear + 1;
+            fclear = f;
         }
     }
 
@@ -331,13 +398,13 @@ __global__ __launch_bounds__(PM_THREADS, 2) void gemm_pm_kernel(
     // main GEMM: lane l, register r -> row 8 (r/4) + 4 (l/32) + r%4, col l%32.
     const float alpha = a_dec[0] * b_dec[0];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < TM; ++i) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int64_t n = n0 + wn * 64 + j * 32 + (lane & 31);
+        for (int j = 0; j < TN; ++j) {
+            const int64_t n = n0 + wn * 32 * TN + j * 32 + (lane & 31);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int64_t m = m0 + wm * 64 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+                const int64_t m = m0 + wm * 32 * TM + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
                 if (m < M && n < N) {
                     const float ct = c[i][j][r] * amul;
                     const float q = grid_d != 0.0f ? __builtin_rintf(ct * grid_d) * inv_grid_d : ct;
@@ -355,20 +422,39 @@ __global__ __launch_bounds__(PM_THREADS, 2) void gemm_pm_kernel(
     }
 }
 
+template <int BMODE, int TT, bool OUT_BF16>
+hipError_t launch_pm_tile(int64_t M, int64_t N, int64_t K, const uint8_t* a, const uint8_t* as, const float* ad,
+                          const uint8_t* b, const uint8_t* bs, const float* bd, void* c, float amul, float grid_d,
+                          hipStream_t s) {
+    const int64_t tm = (M + 64 * TT - 1) / (64 * TT), tn = (N + 64 * TT - 1) / (64 * TT);
+    if (tm * tn > (int64_t)0x7FFFFFFF) return hipErrorInvalidValue;
+    const float inv = grid_d != 0.0f ? 1.0f / grid_d : 0.0f;
+    if (K % 64 == 0)
+        hipLaunchKernelGGL((gemm_pm_kernel<BMODE, TT, TT, OUT_BF16, true>), dim3((unsigned)(tm * tn)),
+                           dim3(PM_THREADS), 0, s, M, N, K, (int)tm, (int)tn, a, as, ad, b, bs, bd, c, amul, grid_d,
+                           inv);
+    else
+        hipLaunchKernelGGL((gemm_pm_kernel<BMODE, TT, TT, OUT_BF16, false>), dim3((unsigned)(tm * tn)),
+                           dim3(PM_THREADS), 0, s, M, N, K, (int)tm, (int)tn, a, as, ad, b, bs, bd, c, amul, grid_d,
+                           inv);
+    return hipGetLastError();
+}
+
 template <int BMODE, bool OUT_BF16>
 hipError_t launch_pm_t(int64_t M, int64_t N, int64_t K, const uint8_t* a, const uint8_t* as,
                        const float* ad, const uint8_t* b, const uint8_t* bs, const float* bd, void* c,
                        float amul, float grid_d, hipStream_t s) {
-    const int64_t tm = (M + PM_BM - 1) / PM_BM, tn = (N + PM_BN - 1) / PM_BN;
-    if (tm * tn > (int64_t)0x7FFFFFFF) return hipErrorInvalidValue;
-    const float inv = grid_d != 0.0f ? 1.0f / grid_d : 0.0f;
-    if (K % 64 == 0)
-        hipLaunchKernelGGL((gemm_pm_kernel<BMODE, OUT_BF16, true>), dim3((unsigned)(tm * tn)), dim3(PM_THREADS),
-                           0, s, M, N, K, (int)tm, (int)tn, a, as, ad, b, bs, bd, c, amul, grid_d, inv);
-    else
-        hipLaunchKernelGGL((gemm_pm_kernel<BMODE, OUT_BF16, false>), dim3((unsigned)(tm * tn)), dim3(PM_THREADS),
-                           0, s, M, N, K, (int)tm, (int)tn, a, as, ad, b, bs, bd, c, amul, grid_d, inv);
-    return hipGetLastError();
+    // 64 x 64 tiles while 128 x 128 ones would not give every CU one
+    // (measured, fprop / dgrad / wgrad, us, large then small: 128 tiles, 1024 x
+    // 2048 x 2048: 75 / 48 / - and 44 / 31 / -; 256 tiles, 2048 x 2048 x 2048:
+    // 74 / 49 / 73 and 69 / 53 / 72; 1024 tiles, K = 4096: 395 and 469)
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    const bool small = ((M + 127) / 128) * ((N + 127) / 128) < cus;
+    return small ? launch_pm_tile<BMODE, 1, OUT_BF16>(M, N, K, a, as, ad, b, bs, bd, c, amul, grid_d, s)
+                 : launch_pm_tile<BMODE, 2, OUT_BF16>(M, N, K, a, as, ad, b, bs, bd, c, amul, grid_d, s);
 }
 
 }  // namespace
