@@ -871,7 +871,8 @@ __device__ __forceinline__ void store_item(f32x16_t (&acc)[4][4], const WorkItem
         const int m = mrow + 32 * i;
         const uint32_t rbase = ((uint32_t)m * (uint32_t)N + (uint32_t)ncol) * esz;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < 4; ++j) {
+            asm volatile("" : "+v"(acc[i][j]));          // read out here, once
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int n = ncol + 32 * j + 8 * g;
@@ -891,7 +892,8 @@ __device__ __forceinline__ void store_item(f32x16_t (&acc)[4][4], const WorkItem
                     }
                 }
             }
-        __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
 }
 
@@ -1103,80 +1105,27 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_reg_kernel(
 // v_mfma_scale_f32_32x32x64_f8f6f4 with both formats E2M1: lane l supplies
 // row l%32 and k = 32(l/32) .. +31 as 16 payload bytes (the stored order),
 // plus the E8M0 byte of that row and k-half; the product of the two scale
-// powers is exact and the accumulation is binary32.  Same tiles, stages,
-// persistent items and epilogue as the register-decode kernel; a stage row
-// holds 128 payload bytes and 8 scale bytes (256 k).
-constexpr int kMxScaleStage = kSupRows * 8;               // 4 KB of scales per stage
-constexpr int kMxScLoads = 4;                             // 4 x 256 B per wave
-constexpr int kMxLoads = kSupPayLoads + kMxScLoads;
+// powers is exact and the accumulation is binary32.  Tiles, persistent items,
+// split tails and epilogue as in the register-decode kernel.
+//
+// Bound: the matrix pipe (32 cycles per product) and, close behind, the
+// 64 bytes per cycle at which a CU takes in operands: 68 KB per 256 k of a
+// tile are 1090 of its 2048 product cycles.  The pipe only stays fed when
+// nothing else comes in bursts, so the LDS reads of each slice and the direct
+// loads are spread between the products, and the two stages of a stage pair
+// share one load of scale codes.  Measured, 8192 x 6144 x 4096 / 8192 x 4096 x
+// 6144 to bf16 / 6144 x 4096 x 8192 to fp32 on one box, us: loads in two bursts
+// per stage and scales gathered per stage 138 / 126 / 150, now 119 / 111 / 136.
+// A ring of four 128-k stages (64-byte rows, two loads per line) took 168 /
+// 156 / 186.  What is left beside the products is the epilogue and the item
+// start, which nothing overlaps, and waits for the slowest load of a stage.
+constexpr int kMxScl = kSupRows * 16;                     // 8 KB: the codes of two stages
 
-// 4 bytes per lane from rsrc at voff + soff into LDS at lds + OFF + 4 lane.
-template <int OFF>
-__device__ __forceinline__ void dma_buf_x1(i32x4_t rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-    asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dword %0, %1, %2 offen lds"
-                 :: "v"(voff), "s"(rsrc), "s"(soff), "s"(lds), "i"(OFF) : "memory", "m0", "scc");
-}
-
-// Per-lane load sources of one tile: first payload chunk; the scale bytes
-// of rows x0 + 32u + l/2 (dword l%2 of their 8 stage bytes), u = 0..3.
-struct MxSrc {
-    uint32_t off0;
-    uint32_t so[4];
-};
-
-struct MxLoader {
-    i32x4_t pay, sca;
-    uint32_t rows8;          // bytes of 8 payload rows
-    uint32_t ldp, lds;       // this wave's LDS offsets inside a payload / scale stage
-
-    template <int I0, int I1, bool SC>
-    __device__ __forceinline__ void issue(uint32_t P, uint32_t S, const MxSrc& src, int G) const {
-        const uint32_t gp = (uint32_t)G * kSupRowBytes;
-        const uint32_t pl = P + ldp;
-        static_for<I0, I1>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            dma_buf_x4<i * 1024>(pay, src.off0 + i * rows8, gp, pl);
-        });
-        if (SC) {
-            const uint32_t gs = (uint32_t)G * 8;
-            const uint32_t sl = S + lds;
-            dma_buf_x1<0>(sca, src.so[0], gs, sl);
-            dma_buf_x1<256>(sca, src.so[1], gs, sl);
-            dma_buf_x1<512>(sca, src.so[2], gs, sl);
-            dma_buf_x1<768>(sca, src.so[3], gs, sl);
-        }
-    }
-};
-
-// One slice of a lane's operands: 16 payload bytes of each of its 4 A and 4
-// B rows (groups 0..3 = A rows 32i + l%32, 4..7 = B rows 32j + l%32).
+// One slice (64 k) of a lane's operands: 16 payload bytes of each of its 4 A
+// and 4 B rows (groups 0..3 = A rows 32i + l%32, 4..7 = B rows 32j + l%32).
 struct MxSlice {
     uint32_t w[8][4];
 };
-
-template <int SL>
-__device__ __forceinline__ void read_mx_slice(MxSlice& R, const uint8_t* P, int pa, int pb, int xo) {
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-        const int row_off = (g < 4 ? pa : pb) + (g & 3) * 32 * kSupRowBytes;
-        const uint4 v = *reinterpret_cast<const uint4*>(P + row_off + xo);
-        R.w[g][0] = v.x; R.w[g][1] = v.y; R.w[g][2] = v.z; R.w[g][3] = v.w;
-    }
-}
-
-// The 8 scale bytes (256 k) of each of the lane's 8 rows, shifted right by
-// one byte in the upper lane half so that, for slice SL, the lane's byte
-// (2 SL + l/32) sits at byte 2 (SL % 2) of dword SL / 2.
-__device__ __forceinline__ void read_mx_scales(uint32_t (&sc)[8][2], const uint8_t* S, int ra, int rb,
-                                               int hi) {
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-        const int row = (g < 4 ? ra : rb) + (g & 3) * 32;
-        const uint2 v = *reinterpret_cast<const uint2*>(S + row * 8);
-        sc[g][0] = v.x >> (8 * hi);
-        sc[g][1] = v.y >> (8 * hi);
-    }
-}
 
 // One scaled FP4 product accumulated in place.  Written as an instruction
 // with a read-write accumulator operand: the compiler's builtin for it has no
@@ -1185,30 +1134,23 @@ __device__ __forceinline__ void read_mx_scales(uint32_t (&sc)[8][2], const uint8
 // of both scale registers.
 typedef int i32x4v_t __attribute__((ext_vector_type(4)));
 template <int SEL>
-__device__ __forceinline__ void mfma_mx(f32x16_t& acc, const i32x4v_t& a, const i32x4v_t& b, uint32_t sa,
+__device__ __forceinline__ void mfma_mx(f32x16_t& acc, const uint32_t (&a)[4], const uint32_t (&b)[4], uint32_t sa,
                                         uint32_t sb) {
     static_assert(SEL == 0 || SEL == 2, "scale byte 0 or 2");
-    // volatile: kept in program order with the waits placed after them
+    const i32x4v_t av = {(int)a[0], (int)a[1], (int)a[2], (int)a[3]};
+    const i32x4v_t bv = {(int)b[0], (int)b[1], (int)b[2], (int)b[3]};
+    // volatile: kept in program order with the loads and waits between them
     if (SEL == 0)
         asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0] cbsz:4 blgp:4"
-                     : "+a"(acc) : "v"(a), "v"(b), "v"(sa), "v"(sb));
+                     : "+a"(acc) : "v"(av), "v"(bv), "v"(sa), "v"(sb));
     else
         asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[1,1,0] cbsz:4 blgp:4"
-                     : "+a"(acc) : "v"(a), "v"(b), "v"(sa), "v"(sb));
+                     : "+a"(acc) : "v"(av), "v"(bv), "v"(sa), "v"(sb));
 }
 
-template <int SL>
-__device__ __forceinline__ void mfma_mx16(f32x16_t (&acc)[4][4], const MxSlice& R, const uint32_t (&sc)[8][2]) {
-    constexpr int d = SL / 2, sel = 2 * (SL % 2);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const i32x4v_t a = {(int)R.w[4 + j][0], (int)R.w[4 + j][1], (int)R.w[4 + j][2], (int)R.w[4 + j][3]};
-            const i32x4v_t b = {(int)R.w[i][0], (int)R.w[i][1], (int)R.w[i][2], (int)R.w[i][3]};
-            // products issued as B x A^T (see store_item)
-            mfma_mx<sel>(acc[i][j], a, b, sc[4 + j][d], sc[i][d]);
-        }
+// The wave's loads and LDS accesses done, then the workgroup barrier.
+__device__ __forceinline__ void wait_all_barrier() {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 template <bool OUT_BF16, bool VEC>
@@ -1217,10 +1159,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_mx_kernel(
     const uint8_t* __restrict__ A, const uint8_t* __restrict__ As, const float* __restrict__ a_dec,
     const uint8_t* __restrict__ B, const uint8_t* __restrict__ Bs, const float* __restrict__ b_dec,
     void* __restrict__ C) {
-    __shared__ __attribute__((aligned(16))) uint8_t sP0[kSupPayload];
-    __shared__ __attribute__((aligned(16))) uint8_t sP1[kSupPayload];
-    __shared__ __attribute__((aligned(16))) uint8_t sC0[kMxScaleStage];
-    __shared__ __attribute__((aligned(16))) uint8_t sC1[kMxScaleStage];
+    __shared__ __attribute__((aligned(16))) uint8_t sP[2 * kSupPayload];
+    __shared__ __attribute__((aligned(16))) uint8_t sC[2 * kMxScl];
     __shared__ __attribute__((aligned(16))) uint8_t sE[kGemmThreads / 64 * kEpiBytes];
 
     const int tid = threadIdx.x;
@@ -1231,41 +1171,9 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_mx_kernel(
 
     const int kb32 = K / 32;                         // scale bytes per row
     const int NG = K / (kSupK * BK);                 // stages of a whole tile
+    const uint32_t rowb = (uint32_t)(K / 2);
 
-    // Loads: waves 0, 1 bring A stage rows 0..255, waves 2, 3 B rows 256..511.
-    const bool isA = wave < 2;
-    const int xw = 128 * (wave & 1);
-    MxLoader L;
-    L.pay = isA ? buffer_rsrc(A, (uint32_t)M * (uint32_t)(K / 2)) : buffer_rsrc(B, (uint32_t)N * (uint32_t)(K / 2));
-    L.sca = isA ? buffer_rsrc(As, (uint32_t)M * kb32) : buffer_rsrc(Bs, (uint32_t)N * kb32);
-    L.rows8 = (uint32_t)(8 * (K / 2));
-    L.ldp = (uint32_t)(128 * wave * kSupRowBytes);
-    L.lds = (uint32_t)(128 * wave * 8);
-    const uint32_t chunk16 = (uint32_t)(((lane & 7) ^ ((lane >> 3) & 7)) * 16);
-    const int rmax = (isA ? M : N) - 1;
-    auto src_of = [&](int t) {
-        int64_t m0, n0;
-        tile_origin(t, tiles_m, tiles_n, m0, n0);
-        const int x0 = (int)(isA ? m0 : n0) + xw;
-        MxSrc q;
-        q.off0 = (uint32_t)(x0 + (lane >> 3)) * (uint32_t)(K / 2) + chunk16;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            q.so[u] = (uint32_t)min(x0 + 32 * u + (lane >> 1), rmax) * (uint32_t)kb32 + 4u * (lane & 1);
-        return q;
-    };
-    const uint32_t P0 = lds_addr(sP0), P1 = lds_addr(sP1), S0 = lds_addr(sC0), S1 = lds_addr(sC1);
-
-    // Read offsets of the lane: first A / B stage rows and per-slice chunk.
-    const int ra = wm * 128 + r, rb = BM + wn * 128 + r;
-    const int pa = ra * kSupRowBytes, pb = rb * kSupRowBytes;
-    const int x0 = ((0 + hi) ^ (r & 7)) * 16, x1 = ((2 + hi) ^ (r & 7)) * 16;
-    const int x2 = ((4 + hi) ^ (r & 7)) * 16, x3 = ((6 + hi) ^ (r & 7)) * 16;
-
-    f32x16_t acc[4][4];
-    MxSlice R0, R1;
-    uint32_t SC0[8][2], SC1[8][2];
-
+    // Items of this workgroup (see gemm_fp4_reg_kernel).
     const int grid = (int)gridDim.x;
     const int nw = (items - (int)blockIdx.x + grid - 1) / grid;
     const int last_it = (int)blockIdx.x + (nw - 1) * grid;
@@ -1274,109 +1182,174 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_mx_kernel(
         return rot ? (k == 0 ? last_it : (int)blockIdx.x + (k - 1) * grid) : (int)blockIdx.x + k * grid;
     };
 
-    {
-        const WorkItem w = work_item(item_at(0), sp, NG);
-        const MxSrc q = src_of(w.t);
-        L.issue<0, kSupPayLoads, true>(P0, S0, q, w.g0);
-        L.issue<0, kSupPayLoads, true>(P1, S1, q, min(w.g0 + 1, w.g1 - 1));
-        wait_vmem<kMxLoads>();
-        __syncthreads();
-    }
+    // ---- loads: a cursor over the stages of the items to come -----------------
+    // Waves 0, 1 bring A stage rows 0..255, waves 2, 3 B rows 256..511: 128
+    // rows each.  Payload load i: rows 8i + l/8, position l%8, which holds
+    // chunk (l%8) ^ (l/8).  Scale load u: 16 codes of row 64u + l, those of
+    // stages 2G and 2G + 1, when the cursor enters such a pair (one load for
+    // 64 rows instead of four gathers of 4 bytes).  Payload rows past the matrix are dropped by the buffer,
+    // scale rows clamped; the second half of an odd row's last pair lies past
+    // the row (the buffer's range check sees the whole per-lane offset) and is
+    // not used.  Past the last item the cursor stays on its last stage.
+    const bool isA = wave < 2;
+    const int xw = 128 * (wave & 1);
+    const i32x4_t pay = isA ? buffer_rsrc(A, (uint32_t)M * rowb) : buffer_rsrc(B, (uint32_t)N * rowb);
+    const i32x4_t sca = isA ? buffer_rsrc(As, (uint32_t)M * kb32) : buffer_rsrc(Bs, (uint32_t)N * kb32);
+    const int rmax = (isA ? M : N) - 1;
+    const uint32_t chunk16 = (uint32_t)(((lane & 7) ^ ((lane >> 3) & 7)) * 16);
+    const uint32_t P0 = lds_addr(sP) + 128u * kSupRowBytes * wave, S0 = lds_addr(sC) + 2048u * wave;
+    struct Source {
+        int g, g1;                                   // stage, one past the item's last
+        uint32_t off, so[2];                         // first payload chunk, scale rows
+    };
+    auto source = [&](int k) {
+        const WorkItem w = work_item(item_at(k), sp, NG);
+        int64_t m0, n0;
+        tile_origin(w.t, tiles_m, tiles_n, m0, n0);
+        const int x0 = (int)(isA ? m0 : n0) + xw;
+        Source q;
+        q.g = w.g0;
+        q.g1 = w.g1;
+        q.off = (uint32_t)(x0 + (lane >> 3)) * rowb + chunk16;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) q.so[u] = (uint32_t)min(x0 + 64 * u + lane, rmax) * (uint32_t)kb32;
+        return q;
+    };
+    Source ls = source(0);
+    int lk = 0, lsb = 0;                             // cursor's item, scale buffer of its stage
+    // payload load i of the cursor's stage into buffer b
+    auto load = [&](auto ic, int b) {
+        constexpr int i = decltype(ic)::value;
+        dma_buf_x4<i * 1024>(pay, ls.off + i * 8 * rowb, (uint32_t)ls.g * kSupRowBytes,
+                             P0 + (uint32_t)(b * kSupPayload));
+    };
+    auto load_scales = [&]() {
+        const uint32_t at = (uint32_t)(ls.g >> 1) * 16u, to = S0 + (uint32_t)(lsb * kMxScl);
+        dma_buf_x4<0>(sca, ls.so[0] + at, 0u, to);
+        dma_buf_x4<1024>(sca, ls.so[1] + at, 0u, to);
+    };
+    // one stage on, with the scales of the pair of stages it enters
+    auto advance = [&]() {
+        bool enters = false;
+        if (ls.g + 1 < ls.g1) {
+            ++ls.g;
+            enters = (ls.g & 1) == 0;
+        } else if (lk + 1 < nw) {
+            ls = source(++lk);
+            enters = true;
+        }
+        if (enters) {
+            lsb ^= 1;
+            load_scales();
+        }
+    };
 
-    for (int k = 0;; ++k) {
-        const int it = item_at(k);
-        const WorkItem cur = work_item(it, sp, NG);
-        const MxSrc scur = src_of(cur.t);
-        const bool has_next = k + 1 < nw;
-        const WorkItem nxt = work_item(has_next ? item_at(k + 1) : it, sp, NG);
-        const MxSrc snxt = src_of(nxt.t);
+    // ---- fragment reads ----------------------------------------------------------
+    const int ra = wm * 128 + r, rb = BM + wn * 128 + r;
+    const uint8_t* const pa = sP + ra * kSupRowBytes;
+    const uint8_t* const pb = sP + rb * kSupRowBytes;
+    const int x0 = ((0 + hi) ^ (r & 7)) * 16, x1 = ((2 + hi) ^ (r & 7)) * 16;
+    const int x2 = ((4 + hi) ^ (r & 7)) * 16, x3 = ((6 + hi) ^ (r & 7)) * 16;
+    auto read_group = [&](MxSlice& R, int g, int b, int xo) {
+        const uint4 v =
+            *reinterpret_cast<const uint4*>((g < 4 ? pa : pb) + (b * kSupPayload + xo) + (g & 3) * 32 * kSupRowBytes);
+        R.w[g][0] = v.x; R.w[g][1] = v.y; R.w[g][2] = v.z; R.w[g][3] = v.w;
+    };
+    // at: scale buffer and half of the pair
+    auto read_scale = [&](uint2& sc, int g, int at) {
+        sc = *reinterpret_cast<const uint2*>(sC + at + ((g < 4 ? ra : rb) + (g & 3) * 32) * 16);
+    };
+
+    f32x16_t acc[4][4];
+    MxSlice R0, R1;
+    uint32_t sc[8][2];
+    uint2 scn[8];
+
+    // stage 0 complete everywhere, stage 1 in flight
+    load_scales();
+    static_for<0, kSupPayLoads>([&](auto ic) { load(ic, 0); });
+    wait_all_barrier();
+    {
+        const int at = (ls.g & 1) * 8;
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {
+            read_group(R0, g, 0, x0);
+            read_scale(scn[g], g, at);
+        }
+    }
+    advance();
+    static_for<0, kSupPayLoads>([&](auto ic) { load(ic, 1); });
+
+    int b = 0, sb = 0;                               // payload and scale buffers of the current stage
+    for (int k = 0; k < nw; ++k) {
+        const WorkItem cur = work_item(item_at(k), sp, NG);
+        const int next_g0 = work_item(item_at(min(k + 1, nw - 1)), sp, NG).g0;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-        read_mx_slice<0>(R0, sP0, pa, pb, x0);
-        read_mx_scales(SC0, sC0, ra, rb, hi);
-        // the products are instructions the compiler does not model: keep
-        // the accumulator and scale writes above clear of the first ones
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_nop 4" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-        const int gshift = has_next ? nxt.g0 - cur.g1 : -1;
-        const int gclamp = has_next ? 0x7FFFFFFF : cur.g1 - 1;
-
-        auto issue_for = [&](auto I0c, auto I1c, auto SCk, uint32_t ldP, uint32_t ldS, int Gt) {
-            constexpr int I0v = decltype(I0c)::value, I1v = decltype(I1c)::value;
-            constexpr bool SCv = decltype(SCk)::value;
-            const bool in_cur = Gt < cur.g1;
-            const int Gl = in_cur ? Gt : min(Gt + gshift, gclamp);
-            MxSrc q;
-            q.off0 = in_cur ? scur.off0 : snxt.off0;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) q.so[u] = in_cur ? scur.so[u] : snxt.so[u];
-            L.issue<I0v, I1v, SCv>(ldP, ldS, q, Gl);
-        };
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) asm volatile("" : "+a"(acc[i][j]));
 
-        // One slice: 16 products on the current slice while the next slice
-        // (or, at slice 3, after the stage barrier, the next stage's slice 0
-        // and scales) is read and, at slice 3, the loads of stage G+2 go out.
-        auto slice = [&](auto SLc, int G, const uint8_t* Pc, const uint8_t* Pn, const uint8_t* Sn,
-                         uint32_t ldP, uint32_t ldS, MxSlice& Rc, MxSlice& Rn, uint32_t (&SCc)[8][2],
-                         uint32_t (&SCn)[8][2]) {
-            constexpr int SL = decltype(SLc)::value;
-            using Z = std::integral_constant<int, 0>;
-            using C8 = std::integral_constant<int, 8>;
-            using CP = std::integral_constant<int, kSupPayLoads>;
-            using F = std::integral_constant<bool, false>;
-            using T = std::integral_constant<bool, true>;
-            if (SL == 3) {
-                wait_vmem<0>();
-                __syncthreads();
-                read_mx_slice<0>(Rn, Pn, pa, pb, x0);
-                read_mx_scales(SCn, Sn, ra, rb, hi);
-                issue_for(Z{}, C8{}, F{}, ldP, ldS, G + 2);
-            } else {
-                read_mx_slice<SL + 1>(Rn, Pc, pa, pb, SL == 0 ? x1 : (SL == 1 ? x2 : x3));
+        for (int st = cur.g0; st < cur.g1; ++st) {
+            // slice SL takes bytes 2 SL + l/32 of each row's 8 codes: dword SL / 2
+            // shifted by the lane half, byte 0 or 2
+#pragma unroll
+            for (int g = 0; g < 8; ++g) {
+                sc[g][0] = scn[g].x >> (8 * hi);
+                sc[g][1] = scn[g].y >> (8 * hi);
             }
-            mfma_mx16<SL>(acc, Rc, SCc);
-            if (SL == 3) {
-                issue_for(C8{}, CP{}, T{}, ldP, ldS, G + 2);
-                // The products are instructions the compiler does not model:
-                // whatever it places after a stage (spills of accumulators,
-                // the epilogue) must not read them before the last ones have
-                // landed.  The wait overlaps the queued products.
-                asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-            }
+            // the products are instructions the compiler does not model: keep
+            // the accumulator and scale writes clear of them
             __builtin_amdgcn_sched_barrier(0);
-        };
-        using I0 = std::integral_constant<int, 0>;
-        using I1 = std::integral_constant<int, 1>;
-        using I2 = std::integral_constant<int, 2>;
-        using I3 = std::integral_constant<int, 3>;
-        // stage scales alternate between SC0 (even stages) and SC1 (odd)
-        auto stage = [&](int G, const uint8_t* Pc, const uint8_t* Pn, const uint8_t* Sn, uint32_t ldP,
-                         uint32_t ldS, uint32_t (&SCc)[8][2], uint32_t (&SCn)[8][2]) {
-            slice(I0{}, G, Pc, Pn, Sn, ldP, ldS, R0, R1, SCc, SCn);
-            slice(I1{}, G, Pc, Pn, Sn, ldP, ldS, R1, R0, SCc, SCn);
-            slice(I2{}, G, Pc, Pn, Sn, ldP, ldS, R0, R1, SCc, SCn);
-            slice(I3{}, G, Pc, Pn, Sn, ldP, ldS, R1, R0, SCc, SCn);
-        };
-        int G = cur.g0;
-        for (; G + 1 < cur.g1; G += 2) {
-            stage(G, sP0, sP1, sC1, P0, S0, SC0, SC1);
-            stage(G + 1, sP1, sP0, sC0, P1, S1, SC1, SC0);
+            asm volatile("s_nop 4" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            // 16 products on Rc (issued as B x A^T, see store_item) with the
+            // reads of the next slice and, in slice 3, the loads of the stage
+            // after the next spread between them.  (Half of those loads in
+            // slice 0 instead leaves them too little time: 121 us against 112
+            // for the shape above.)
+            const int bn = b ^ 1;
+            const bool last = st + 1 == cur.g1;
+            const int gn = last ? next_g0 : st + 1;              // the next stage and its scale buffer
+            const int sbn = last || (gn & 1) == 0 ? sb ^ 1 : sb;
+            const int at = sbn * kMxScl + (gn & 1) * 8;
+            auto slice = [&](auto SLc, MxSlice& Rc, MxSlice& Rn, int rbuf, int xo) {
+                constexpr int SL = decltype(SLc)::value;
+                static_for<0, 16>([&](auto qc) {
+                    constexpr int q = decltype(qc)::value, i = q / 4, j = q % 4;
+                    mfma_mx<2 * (SL % 2)>(acc[i][j], Rc.w[4 + j], Rc.w[i], sc[4 + j][SL / 2], sc[i][SL / 2]);
+                    if constexpr (q % 2 == 0) {
+                        read_group(Rn, q / 2, rbuf, xo);
+                        if constexpr (SL == 3) read_scale(scn[q / 2], q / 2, at);
+                    }
+                    if constexpr (SL == 3) load(qc, b);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            };
+            using I0 = std::integral_constant<int, 0>;
+            using I1 = std::integral_constant<int, 1>;
+            using I2 = std::integral_constant<int, 2>;
+            using I3 = std::integral_constant<int, 3>;
+            slice(I0{}, R0, R1, b, x1);
+            slice(I1{}, R1, R0, b, x2);
+            slice(I2{}, R0, R1, b, x3);
+            // every wave has read this stage, the next one has landed
+            wait_all_barrier();
+            advance();
+            slice(I3{}, R1, R0, bn, x0);
+            b = bn;
+            sb = sbn;
         }
-        if (G < cur.g1) stage(G, sP0, sP1, sC1, P0, S0, SC0, SC1);   // odd stage count (single item)
-
-        // the products above are instructions the compiler does not model:
-        // give the last ones time to land before their results are read
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+        // give the last products time to land before their results are read
+        asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         store_item<OUT_BF16, VEC>(acc, cur, sp, M, N, tiles_m, tiles_n, wave, lane, a_dec[0] * b_dec[0], C,
                                   sE + wave * kEpiBytes);
-        if (!has_next) break;
     }
     wait_vmem<0>();                                  // no load outlives the kernel's LDS
 }
@@ -1542,7 +1515,7 @@ hipError_t launch_mx(int64_t M, int64_t N, int64_t K, const uint8_t* a, const ui
         }
     }
     const int items = sp.Tdp + (T - sp.Tdp) * sp.parts;
-    const int grid = (even && cus > 0) ? min(items, cus) : items;
+    const int grid = min(items, cus);                // persistent, whatever the stage counts
     if (vector_epilogue<OUT_BF16>(N, tiles_m))
         hipLaunchKernelGGL((gemm_mx_kernel<OUT_BF16, true>), dim3((unsigned)grid), dim3(kGemmThreads), 0, s, (int)M,
                            (int)N, (int)K, tiles_m, tiles_n, items, sp, a, as, ad, b, bs, bd, c);
