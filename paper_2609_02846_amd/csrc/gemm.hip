@@ -1405,26 +1405,45 @@ hipError_t split_workspace(hipStream_t s, size_t part_floats, float** part) {
     return e;
 }
 
-// Block-32 scale codes to the block-16 layout the decode kernels read:
-// out[r][j] = in[r / rrep][j / 2] (rrep 2 for 32 x 32 tile scales, whose
-// tile rows cover two 16-row tile rows).
-__global__ __launch_bounds__(256) void expand_scales_kernel(const uint8_t* __restrict__ in, int64_t cols_in,
-                                                            int rrep, uint8_t* __restrict__ out,
-                                                            int64_t rows_out, int64_t cols_out) {
-    const int64_t n = rows_out * cols_out;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        const int64_t r = i / cols_out, j = i - r * cols_out;
-        out[i] = in[(r / rrep) * cols_in + j / 2];
+// Scale codes of one operand copied to the layout a kernel reads: out row r
+// (of rows) holds, at column c < cols, code c >> shift of input row r / rrep,
+// and zeros up to its stride.
+struct ScaleCopy {
+    const uint8_t* in;
+    uint8_t* out;
+    int64_t rows, cols, stride, cols_in;
+    int shift, rrep;
+};
+
+// Both operands' scale codes in one launch: the first `a_blocks` workgroups
+// walk A, the others B.  Latency-bound (a few MB at most; two launches of a
+// byte per thread took 5 and 3 us for 4096 x 4096 operands): 4 codes per
+// thread where the row stride allows it.
+__global__ __launch_bounds__(256) void copy_scales_kernel(ScaleCopy a, ScaleCopy b, int a_blocks) {
+    const bool is_a = (int)blockIdx.x < a_blocks;
+    const ScaleCopy s = is_a ? a : b;
+    const int64_t first = (int64_t)(is_a ? blockIdx.x : blockIdx.x - a_blocks) * 256 + threadIdx.x;
+    const int64_t step = (int64_t)(is_a ? a_blocks : gridDim.x - a_blocks) * 256;
+    auto code = [&](int64_t r, int64_t c) -> uint32_t {
+        return c < s.cols ? s.in[(r / s.rrep) * s.cols_in + (c >> s.shift)] : 0u;
+    };
+    if ((s.stride & 3) == 0) {
+        const uint32_t per = (uint32_t)(s.stride >> 2);
+        for (int64_t i = first; i < s.rows * per; i += step) {
+            const int64_t r = i / per, c = 4 * (i - r * per);
+            reinterpret_cast<uint32_t*>(s.out)[i] =
+                code(r, c) | code(r, c + 1) << 8 | code(r, c + 2) << 16 | code(r, c + 3) << 24;
+        }
+    } else {
+        for (int64_t i = first; i < s.rows * s.stride; i += step)
+            s.out[i] = (uint8_t)code(i / s.stride, i % s.stride);
     }
 }
 
-hipError_t expand_scales(const uint8_t* in, int64_t cols_in, int rrep, uint8_t* out, int64_t rows_out,
-                         int64_t cols_out, hipStream_t s) {
-    const int64_t n = rows_out * cols_out;
-    if (n <= 0) return hipSuccess;
-    const int64_t blocks = min((n + 255) / 256, (int64_t)4096);
-    hipLaunchKernelGGL(expand_scales_kernel, dim3((unsigned)blocks), dim3(256), 0, s, in, cols_in, rrep, out,
-                       rows_out, cols_out);
+hipError_t copy_scales(const ScaleCopy& a, const ScaleCopy& b, hipStream_t s) {
+    auto blocks = [](const ScaleCopy& c) { return (int)min(max((c.rows * c.stride / 4 + 255) / 256, (int64_t)1), (int64_t)2048); };
+    const int na = blocks(a), nb = blocks(b);
+    hipLaunchKernelGGL(copy_scales_kernel, dim3((unsigned)(na + nb)), dim3(256), 0, s, a, b, na);
     return hipGetLastError();
 }
 
@@ -1645,8 +1664,11 @@ hipError_t launch_gemm_b32(BScale bmode, float amul, bool pm, float grid_d, int6
         if (e != hipSuccess) return e;
         uint8_t* wa = static_cast<uint8_t*>(ws);
         uint8_t* wb = wa + abytes;
-        if ((e = expand_scales(a_scales, kb32, 1, wa, M, kb16, s)) != hipSuccess) return e;
-        if ((e = expand_scales(b_scales, kb32, tiled ? 2 : 1, wb, brows16, kb16, s)) != hipSuccess) return e;
+        // block-32 codes to the block-16 layout: each code twice along k, and
+        // each 32 x 32 tile row as two 16-row tile rows
+        e = copy_scales({a_scales, wa, M, kb16, kb16, kb32, 1, 1},
+                        {b_scales, wb, brows16, kb16, kb16, kb32, 1, tiled ? 2 : 1}, s);
+        if (e != hipSuccess) return e;
         as16 = wa;
         bs16 = wb;
     }
