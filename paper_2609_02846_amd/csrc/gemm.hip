@@ -14,8 +14,8 @@
 // Kernels of this file (gfx950, one 256-thread workgroup per CU, 256 x 256
 // output tiles, four waves of 128 x 128 in a 2 x 2 grid, 16
 // v_mfma_f32_32x32x16_f16 accumulators per wave = all 256 AccVGPRs):
-//  * K % 256 == 0, operands and C below 2^31 bytes: gemm_fp4_reg_kernel,
-//    persistent; packed FP4 rows and scale codes staged in LDS by direct
+//  * operands and C below 2^31 bytes: gemm_fp4_reg_kernel (K % 256 == 0, or
+//    on scale codes copied to rows padded to it), persistent; packed FP4 rows and scale codes staged in LDS by direct
 //    loads four 64-k slices at a time, each wave decoding its own fragments
 //    in registers (no fp16 copy through LDS);
 //  * operands of 2^31 bytes and more (64-bit addresses): gemm_fp4_dma_kernel
@@ -23,8 +23,8 @@
 //    per workgroup into a double-buffered fp16 LDS stage, and
 //    gemm_fp4_kernel for any K % 16 == 0, the same with register-staged
 //    loads (it also writes the zeros of K = 0).
-// Few output rows run in gemm_skinny.hip; calls that fill the chip better in
-// smaller tiles, and every other K, in gemm_mid.hip (launch_mode).
+// Few output rows run in gemm_skinny.hip, calls that fill the chip better in
+// smaller tiles in gemm_mid.hip (launch_mode).
 // Decoding writes each UE5M3 scale s as mu * 2^E (mu = 1 + m/8 in [1, 2), or
 // 0 for code 0) or reads the code as an fp16 bit pattern (c << 7 is its
 // value).  The gfx950 FP4 -> FP16 conversion applies a power-of-two scale
@@ -630,11 +630,13 @@ struct SupLoader {
 
     template <int I0, int I1, bool SC>
     __device__ __forceinline__ void issue(uint32_t P, uint32_t S, const SupSrc& src, int64_t G) const {
-        const uint32_t gp = (uint32_t)G * kSupRowBytes;
+        // the stage offset goes into the per-lane offset, which the buffer's
+        // range check covers: the last row's stage may end past the row
+        const uint32_t vo = src.off0 + (uint32_t)G * kSupRowBytes;
         const uint32_t pl = P + ldp;
         static_for<I0, I1>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
-            dma_buf_x4<i * 1024>(pay, src.off0 + i * rows8, gp, pl);
+            dma_buf_x4<i * 1024>(pay, vo + i * rows8, 0u, pl);
         });
         if (SC) {
             const uint32_t gs = (uint32_t)G * 16;
@@ -904,9 +906,13 @@ __device__ __forceinline__ void store_item(f32x16_t (&acc)[4][4], const WorkItem
 // must have an even number of stages when a workgroup runs more than one
 // (the stage buffers alternate and every item starts in buffer 0).  Sizes:
 // every operand, C and the partial workspace span less than 2^31 bytes.
+// K is a multiple of 256 and rowb the payload row's bytes: K / 2, or less
+// when the operands' K has been rounded up (launch_mode); the scale
+// codes past rowb are then 0, so what is staged past a row's end (the next
+// row's bytes, zeros past the matrix) counts as zeros.
 template <int BMODE, bool OUT_BF16, bool VEC>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_reg_kernel(
-    int M, int N, int K, int tiles_m, int tiles_n, int items, SplitPlan sp,
+    int M, int N, int K, uint32_t rowb, int tiles_m, int tiles_n, int items, SplitPlan sp,
     const uint8_t* __restrict__ A, const uint8_t* __restrict__ As, const float* __restrict__ a_dec,
     const uint8_t* __restrict__ B, const uint8_t* __restrict__ Bs, const float* __restrict__ b_dec,
     void* __restrict__ C, float amul) {
@@ -930,9 +936,9 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_reg_kernel(
     const int xw = 128 * (wave & 1);                 // first stage row of the wave within A or B
     const int brows = BMODE == (int)BScale::Row ? N : (N + 15) / 16;   // rows of the B scale matrix
     SupLoader L;
-    L.pay = isA ? buffer_rsrc(A, (uint32_t)M * kbt * 8) : buffer_rsrc(B, (uint32_t)N * kbt * 8);
+    L.pay = isA ? buffer_rsrc(A, (uint32_t)M * rowb) : buffer_rsrc(B, (uint32_t)N * rowb);
     L.sca = isA ? buffer_rsrc(As, (uint32_t)M * kbt) : buffer_rsrc(Bs, (uint32_t)brows * kbt);
-    L.rows8 = (uint32_t)(64 * kbt);
+    L.rows8 = 8 * rowb;
     L.ldp = (uint32_t)(128 * wave * kSupRowBytes);
     L.lds = (uint32_t)(128 * wave * kSupK * 4);
     const uint32_t chunk16 = (uint32_t)(((lane & 7) ^ ((lane >> 3) & 7)) * 16);
@@ -941,7 +947,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_reg_kernel(
         tile_origin(t, tiles_m, tiles_n, m0, n0);
         const int x0 = (int)(isA ? m0 : n0) + xw;
         SupSrc q;
-        q.off0 = (uint32_t)(x0 + (lane >> 3)) * (uint32_t)(kbt * 8) + chunk16;
+        q.off0 = (uint32_t)(x0 + (lane >> 3)) * rowb + chunk16;
         const int xa = x0 + lane, xb = x0 + 64 + lane;
         if (isA) {
             q.so0 = (uint32_t)min(xa, M - 1) * kbt;
@@ -1459,53 +1465,56 @@ bool vector_epilogue(int64_t N, int tiles_m) {
     return N % 4 == 0;
 }
 
-template <int BMODE, bool OUT_BF16>
-hipError_t launch_reg(int64_t M, int64_t N, int64_t K, const uint8_t* a, const uint8_t* as,
-                      const float* ad, const uint8_t* b, const uint8_t* bs, const float* bd,
-                      void* c, float amul, hipStream_t s, const FixedScratch* fx) {
-    const int tiles_m = (int)((M + BM - 1) / BM);
-    const int tiles_n = (int)((N + BN - 1) / BN);
-    const int T = tiles_m * tiles_n;
+// Floats of split-tile partials that launch_reg's plan needs.
+struct RegPlan {
+    int tiles_m, tiles_n, T, rem, parts;             // rem tiles split into parts (parts > 1)
+    size_t floats;
+};
+
+RegPlan reg_plan(int64_t M, int64_t N, int64_t K, int cus) {
+    RegPlan p;
+    p.tiles_m = (int)((M + BM - 1) / BM);
+    p.tiles_n = (int)((N + BN - 1) / BN);
+    p.T = p.tiles_m * p.tiles_n;
+    p.rem = p.T % cus;
+    p.parts = 1;
+    p.floats = 0;
     const int NG = (int)(K / (kSupK * BK));
-    int dev = 0, cus = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
     // One workgroup per CU at a time (LDS-bound).  Split only a partial last
     // wave of tiles that leaves at least 1 - 1/kSplitRemDiv of the CUs idle;
     // parts cover whole stage pairs when the stage count is even.
-    const bool even = NG % 2 == 0;
-    SplitPlan sp{T, 1, nullptr};
-    const int rem = cus > 0 ? T % cus : 0;
-    if (T > cus && rem > 0 && rem <= cus / kSplitRemDiv) {
-        const int parts = min(cus / rem, even ? NG / 2 : NG);
-        if (parts > 1) {
-            sp.Tdp = T - rem;
-            sp.parts = parts;
-            const size_t need = (size_t)rem * parts * 65536;
-            if (fx != nullptr) {
-                // caller-supplied buffer: the same plan, or a refusal
-                if (need > fx->floats) return hipErrorOutOfMemory;
-                sp.part = fx->part;
-            } else {
-                e = split_workspace(s, need, &sp.part);
-                if (e != hipSuccess) return e;
-            }
-        }
+    if (p.T > cus && p.rem > 0 && p.rem <= cus / kSplitRemDiv) {
+        p.parts = min(cus / p.rem, NG % 2 == 0 ? NG / 2 : NG);
+        if (p.parts > 1) p.floats = (size_t)p.rem * p.parts * 65536;
     }
-    const int items = sp.Tdp + (T - sp.Tdp) * sp.parts;
+    return p;
+}
+
+// K: a multiple of 256 (rounded up when the payload rows of rowb bytes are
+// shorter); part: room for the plan's partials.
+template <int BMODE, bool OUT_BF16>
+hipError_t launch_reg(const RegPlan& p, int cus, float* part, int64_t M, int64_t N, int64_t K, uint32_t rowb,
+                      const uint8_t* a, const uint8_t* as, const float* ad, const uint8_t* b, const uint8_t* bs,
+                      const float* bd, void* c, float amul, hipStream_t s) {
+    const int NG = (int)(K / (kSupK * BK));
+    SplitPlan sp{p.T, 1, nullptr};
+    if (p.parts > 1) sp = SplitPlan{p.T - p.rem, p.parts, part};
+    const int items = sp.Tdp + (p.T - sp.Tdp) * sp.parts;
     // persistent (one workgroup per CU walking the items) when every item has
     // an even stage count, else one item per workgroup
-    const int grid = (even && cus > 0) ? min(items, cus) : items;
-    if (vector_epilogue<OUT_BF16>(N, tiles_m))
+    const int grid = NG % 2 == 0 ? min(items, cus) : items;
+    if (vector_epilogue<OUT_BF16>(N, p.tiles_m))
         hipLaunchKernelGGL((gemm_fp4_reg_kernel<BMODE, OUT_BF16, true>), dim3((unsigned)grid), dim3(kGemmThreads),
-                           0, s, (int)M, (int)N, (int)K, tiles_m, tiles_n, items, sp, a, as, ad, b, bs, bd, c, amul);
+                           0, s, (int)M, (int)N, (int)K, rowb, p.tiles_m, p.tiles_n, items, sp, a, as, ad, b, bs, bd,
+                           c, amul);
     else
         hipLaunchKernelGGL((gemm_fp4_reg_kernel<BMODE, OUT_BF16, false>), dim3((unsigned)grid), dim3(kGemmThreads),
-                           0, s, (int)M, (int)N, (int)K, tiles_m, tiles_n, items, sp, a, as, ad, b, bs, bd, c, amul);
-    if ((e = hipGetLastError()) != hipSuccess || sp.parts == 1) return e;
-    hipLaunchKernelGGL((gemm_split_sum_kernel<BMODE, OUT_BF16>), dim3((unsigned)(64 * (T - sp.Tdp))), dim3(256),
-                       0, s, M, N, tiles_m, tiles_n, sp, ad, bd, c, amul);
+                           0, s, (int)M, (int)N, (int)K, rowb, p.tiles_m, p.tiles_n, items, sp, a, as, ad, b, bs, bd,
+                           c, amul);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || sp.parts == 1) return e;
+    hipLaunchKernelGGL((gemm_split_sum_kernel<BMODE, OUT_BF16>), dim3((unsigned)(64 * (p.T - sp.Tdp))), dim3(256),
+                       0, s, M, N, p.tiles_m, p.tiles_n, sp, ad, bd, c, amul);
     return hipGetLastError();
 }
 
@@ -1600,6 +1609,13 @@ double reg_time(int64_t M, int64_t N, int64_t K, int cus) {
     return t;
 }
 
+// K not a multiple of 256 runs in 256 x 256 tiles on scale codes copied to
+// rows padded with zeros: the copy and its launch, us.  Measured, padded large
+// tiles / small tiles, us: 21504 x 4096 x 7888 1029 / 1271, 6144 x 4096 x 8000
+// 315 / 365, 4096 x 4096 x 4000 112 / 138, 4096 x 4096 x 2064 66 / 73; with few
+// k the small ones stay ahead: 6144 x 4096 x 1040 80 / 59.
+constexpr double kPadUs = 6.0;
+
 template <int BMODE>
 hipError_t launch_mode(int64_t M, int64_t N, int64_t K, const uint8_t* a, const uint8_t* as,
                        const float* ad, const uint8_t* b, const uint8_t* bs, const float* bd,
@@ -1607,17 +1623,58 @@ hipError_t launch_mode(int64_t M, int64_t N, int64_t K, const uint8_t* a, const 
     // the register-decode kernels address operands (and, in 256 x 256 tiles,
     // C) with 32-bit offsets
     const int64_t kLim = (int64_t)1 << 31;
-    const bool reg = K % (4 * BK) == 0 && K > 0 && M * (K / 2) < kLim && N * (K / 2) < kLim && M * N * 4 < kLim;
-    if (mid_gemm_fits(M, N, K)) {
+    const int64_t Kp = (K + 255) / 256 * 256;
+    const bool reg = K > 0 && M * (Kp / 2) < kLim && N * (Kp / 2) < kLim && M * N * 4 < kLim;
+    const bool mid = mid_gemm_fits(M, N, K);
+    if (reg || mid) {
         int cus = 0;
-        const hipError_t e = device_cus(&cus);
+        hipError_t e = device_cus(&cus);
         if (e != hipSuccess) return e;
-        if (!reg || mid_gemm_time(M, N, K, cus) < reg_time(M, N, K, cus))
-            return launch_gemm_mid((BScale)BMODE, amul, M, N, K, cus, a, as, ad, b, bs, bd, c, c_bf16, s);
+        // the cost of K % 256: copying the scale codes to padded rows
+        const bool padded = K % 256 != 0;
+        const bool use_mid = mid && (!reg || mid_gemm_time(M, N, K, cus) <
+                                                 reg_time(M, N, Kp, cus) + (padded ? kPadUs : 0.0));
+        if (reg && !use_mid) {
+            const RegPlan p = reg_plan(M, N, Kp, cus);
+            const uint8_t *as16 = as, *bs16 = bs;
+            const int64_t kb = K / 16, kp = Kp / 16;
+            const int64_t brows = BMODE == (int)BScale::Row ? N : (N + 15) / 16;
+            const size_t abytes = padded ? (size_t)((M * kp + 255) / 256 * 256) : 0;
+            const size_t bbytes = padded ? (size_t)(brows * kp) : 0;
+            const size_t pad_at = (p.floats + 63) / 64 * 64;     // fixed buffer: partials, then padded codes
+            const size_t need = pad_at * sizeof(float) + abytes + bbytes;
+            float* part = nullptr;
+            uint8_t* pad = nullptr;
+            if (fx != nullptr) {
+                e = need <= fx->floats * sizeof(float) ? hipSuccess : hipErrorOutOfMemory;
+                part = fx->part;
+                pad = reinterpret_cast<uint8_t*>(fx->part + pad_at);
+            } else if (!padded || need <= kNoallocBytes) {
+                if (p.floats > 0) e = split_workspace(s, p.floats, &part);
+                void* ws = nullptr;
+                if (e == hipSuccess && padded) e = stream_workspace(kWsPad, s, abytes + bbytes, &ws);
+                pad = static_cast<uint8_t*>(ws);
+            } else {
+                e = hipErrorOutOfMemory;             // as with the fixed buffer, so that both take the same way
+            }
+            if (e == hipSuccess && padded) {
+                e = copy_scales({as, pad, M, kb, kp, kb, 0, 1}, {bs, pad + abytes, brows, kb, kp, kb, 0, 1}, s);
+                if (e != hipSuccess) return e;
+                as16 = pad;
+                bs16 = pad + abytes;
+            }
+            if (e == hipSuccess)
+                return c_bf16 ? launch_reg<BMODE, true>(p, cus, part, M, N, Kp, (uint32_t)(K / 2), a, as16, ad, b, bs16,
+                                                        bd, c, amul, s)
+                              : launch_reg<BMODE, false>(p, cus, part, M, N, Kp, (uint32_t)(K / 2), a, as16, ad, b,
+                                                         bs16, bd, c, amul, s);
+            // No workspace (a capturing stream that has none yet, no slot, no
+            // memory): K % 256 == 0 refuses; a padded call goes on without one.
+            if (!padded) return e;
+            (void)hipGetLastError();
+        }
+        if (mid) return launch_gemm_mid((BScale)BMODE, amul, M, N, K, cus, a, as, ad, b, bs, bd, c, c_bf16, s);
     }
-    if (reg)
-        return c_bf16 ? launch_reg<BMODE, true>(M, N, K, a, as, ad, b, bs, bd, c, amul, s, fx)
-                      : launch_reg<BMODE, false>(M, N, K, a, as, ad, b, bs, bd, c, amul, s, fx);
     if (K % BK == 0 && K > 0)
         return c_bf16 ? launch_dma<BMODE, true>(M, N, K, a, as, ad, b, bs, bd, c, amul, s)
                       : launch_dma<BMODE, false>(M, N, K, a, as, ad, b, bs, bd, c, amul, s);

@@ -400,12 +400,12 @@ struct MidPlan {
 // 1x2x2 23 / 22 (2x2x2 31 / 30, 1x1x2 29 / 25), 777 x 4096 x 21504 2x2x2
 // 153 / 151 (2x2x1 169 / 164, 1x2x1 205 / 190), 100 x 6144 x 4096 1x1x2
 // 17 / 15.5, 1520 x 1360 x 3408 2x2x2 30 / 29, 1520 x 3408 x 1360 2x2x1
-// 26 / 26.  Two K groups (ks = 2) help a CU that has only one tile: with one
+// 27 / 26, 6144 x 4096 x 8000 2x2x1 361 / 365.  Two K groups (ks = 2) help a CU that has only one tile: with one
 // wave per SIMD its decode and products do not overlap fully.
 MidPlan mid_plan(int64_t M, int64_t N, int64_t K, int cus) {
     const MidPlan c[6] = {
-        {2, 2, 1, mid_time(M, N, K, cus, 128, 128, 2.0, 6.8, 7.6)},
-        {2, 2, 2, mid_time(M, N, K, cus, 128, 128, 3.5, 6.8, 6.8)},
+        {2, 2, 1, mid_time(M, N, K, cus, 128, 128, 2.0, 7.2, 7.6)},
+        {2, 2, 2, mid_time(M, N, K, cus, 128, 128, 3.5, 7.2, 6.8)},
         {1, 2, 1, mid_time(M, N, K, cus, 64, 128, 1.7, 4.6, 5.1)},
         {1, 2, 2, mid_time(M, N, K, cus, 64, 128, 2.8, 4.6, 4.2)},
         {1, 1, 1, mid_time(M, N, K, cus, 64, 64, 1.0, 2.9, 3.4)},

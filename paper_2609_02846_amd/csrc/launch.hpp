@@ -21,11 +21,11 @@ enum class ScaleKind : int { UE5M3 = 0, E4M3 = 1, E8M0 = 2 };
 // need and replaced by a larger one on demand (the replaced buffer is kept,
 // not freed, until the process ends): split-tile partials of the GEMMs,
 // block-32 scales expanded to the block-16 layout, per-workgroup partial
-// maxima of the amax kernels.  Uses on one stream are ordered by the
+// maxima of the amax kernels, scale codes in rows padded to 256 k.  Uses on one stream are ordered by the
 // stream, so a buffer is reused by the next call on that stream.  Returns
 // hipErrorStreamCaptureUnsupported when s is capturing and an allocation
 // would be needed.
-enum WorkspaceKind : int { kWsSplit = 0, kWsScales = 1, kWsAmax = 2, kWsKinds = 3 };
+enum WorkspaceKind : int { kWsSplit = 0, kWsScales = 1, kWsAmax = 2, kWsPad = 3, kWsKinds = 4 };
 hipError_t stream_workspace(int kind, hipStream_t s, size_t bytes, void** out);
 
 // *amax_dev = max(clear ? 0 : *amax_dev, max |x|); a kept value must be a
@@ -101,6 +101,12 @@ double mid_gemm_time(int64_t M, int64_t N, int64_t K, int cus);
 hipError_t launch_gemm_mid(BScale bmode, float amul, int64_t M, int64_t N, int64_t K, int cus, const uint8_t* a,
                            const uint8_t* a_scales, const float* a_dec, const uint8_t* b, const uint8_t* b_scales,
                            const float* b_dec, void* c, bool c_bf16, hipStream_t s);
+
+// Bytes of that array: 64 MiB for 256 partial tiles of 256 x 256 fp32, the
+// largest split
+// plan on a device of up to 256 compute units (the leftover tiles times their
+// parts never exceed the unit count), and 16 MiB for padded scale codes.
+constexpr size_t kNoallocBytes = (size_t)80 << 20;
 
 // The allocation-free GEMM's scratch array on the current device: its
 // device address (taken once per device) and capacity in floats.
