@@ -98,7 +98,7 @@ def gemm_source_hash():
     on, and a comment edit does not change that code."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("gemm.hip", "fp4_decode.hpp", "codec.hpp"):
+    for f in ("gemm.hip", "gemm_regs.hpp", "fp4_decode.hpp", "codec.hpp"):
         text = open(os.path.join(ROOT, "paper_2609_02846_amd", "csrc", f), encoding="utf-8").read()
         lines = (ln.split("//")[0].rstrip() for ln in text.splitlines())
         h.update("\n".join(ln for ln in lines if ln).encode())
