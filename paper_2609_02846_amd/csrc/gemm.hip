@@ -1120,7 +1120,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_reg_kernel(
 // nothing else comes in bursts, so the LDS reads of each slice and the direct
 // loads are spread between the products, and the two stages of a stage pair
 // share one load of scale codes.  Measured, 8192 x 6144 x 4096 / 8192 x 4096 x
-// 6144 to bf16 / 6144 x 4096 x 8192 to fp32 on one box, us: loads in two bursts
+// 6144 to bf16 / 6144 x 4096 x 8192 to fp32 on one device, us: loads in two bursts
 // per stage and scales gathered per stage 138 / 126 / 150, now 119 / 111 / 136.
 // A ring of four 128-k stages (64-byte rows, two loads per line) took 168 /
 // 156 / 186.  What is left beside the products is the epilogue and the item
