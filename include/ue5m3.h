@@ -29,7 +29,9 @@
  *   pairs can hold workspaces (a further pair gets UE5M3_EHIP).
  *   ue5m3_gemm_noalloc uses no workspace (see there).  Besides these the
  *   library keeps only caches of device properties.  The library
- *   may be called from several host threads at once.
+ *   may be called from several host threads at once, also on one stream:
+ *   a call enqueues the launches that share a workspace with no other
+ *   call's between them.
  * - Stream capture: a call made while `stream` is capturing that would have
  *   to allocate or grow a workspace returns UE5M3_EHIP and enqueues
  *   nothing; run the same call once before capturing (no library call

@@ -119,8 +119,9 @@ __global__ __launch_bounds__(kAmaxThreads) void amax_rht_kernel(
 template <typename Launch>
 hipError_t amax_two_pass(int64_t blocks, int shift, bool keep, float* amax_dev, hipStream_t s, Launch launch) {
     uint32_t* out = reinterpret_cast<uint32_t*>(amax_dev);
+    Workspace held;
     void* ws = nullptr;
-    hipError_t e = stream_workspace(kWsAmax, s, kAmaxMaxBlocks * sizeof(uint32_t), &ws);
+    hipError_t e = held.take(kWsAmax, s, kAmaxMaxBlocks * sizeof(uint32_t), &ws);
     if (e != hipSuccess) return e;
     uint32_t* part = static_cast<uint32_t*>(ws);
     if (blocks > 0) {

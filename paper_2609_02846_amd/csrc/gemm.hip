@@ -1404,9 +1404,9 @@ __global__ __launch_bounds__(256) void gemm_split_sum_kernel(
     }
 }
 
-hipError_t split_workspace(hipStream_t s, size_t part_floats, float** part) {
+hipError_t split_workspace(Workspace& ws, hipStream_t s, size_t part_floats, float** part) {
     void* p = nullptr;
-    const hipError_t e = stream_workspace(kWsSplit, s, part_floats * sizeof(float), &p);
+    const hipError_t e = ws.take(kWsSplit, s, part_floats * sizeof(float), &p);
     *part = static_cast<float*>(p);
     return e;
 }
@@ -1531,6 +1531,7 @@ hipError_t launch_mx(int64_t M, int64_t N, int64_t K, const uint8_t* a, const ui
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     const bool even = NG % 2 == 0;
+    Workspace held;                                  // until the sum is enqueued
     SplitPlan sp{T, 1, nullptr};
     const int rem = cus > 0 ? T % cus : 0;
     if (T > cus && rem > 0 && rem <= cus / kSplitRemDiv) {
@@ -1538,7 +1539,7 @@ hipError_t launch_mx(int64_t M, int64_t N, int64_t K, const uint8_t* a, const ui
         if (parts > 1) {
             sp.Tdp = T - rem;
             sp.parts = parts;
-            e = split_workspace(s, (size_t)rem * parts * 65536, &sp.part);
+            e = split_workspace(held, s, (size_t)rem * parts * 65536, &sp.part);
             if (e != hipSuccess) return e;
         }
     }
@@ -1643,6 +1644,7 @@ hipError_t launch_mode(int64_t M, int64_t N, int64_t K, const uint8_t* a, const 
             const size_t bbytes = padded ? (size_t)(brows * kp) : 0;
             const size_t pad_at = (p.floats + 63) / 64 * 64;     // fixed buffer: partials, then padded codes
             const size_t need = pad_at * sizeof(float) + abytes + bbytes;
+            Workspace split_ws, pad_ws;              // held until the launches are enqueued
             float* part = nullptr;
             uint8_t* pad = nullptr;
             if (fx != nullptr) {
@@ -1650,9 +1652,9 @@ hipError_t launch_mode(int64_t M, int64_t N, int64_t K, const uint8_t* a, const 
                 part = fx->part;
                 pad = reinterpret_cast<uint8_t*>(fx->part + pad_at);
             } else if (!padded || need <= kNoallocBytes) {
-                if (p.floats > 0) e = split_workspace(s, p.floats, &part);
+                if (p.floats > 0) e = split_workspace(split_ws, s, p.floats, &part);
                 void* ws = nullptr;
-                if (e == hipSuccess && padded) e = stream_workspace(kWsPad, s, abytes + bbytes, &ws);
+                if (e == hipSuccess && padded) e = pad_ws.take(kWsPad, s, abytes + bbytes, &ws);
                 pad = static_cast<uint8_t*>(ws);
             } else {
                 e = hipErrorOutOfMemory;             // as with the fixed buffer, so that both take the same way
@@ -1708,6 +1710,7 @@ hipError_t launch_gemm(BScale bmode, float amul, int64_t M, int64_t N, int64_t K
 hipError_t launch_gemm_b32(BScale bmode, float amul, bool pm, float grid_d, int64_t M, int64_t N, int64_t K,
                            const uint8_t* a, const uint8_t* a_scales, const float* a_dec, const uint8_t* b,
                            const uint8_t* b_scales, const float* b_dec, void* c, bool c_bf16, hipStream_t s) {
+    Workspace held;                                  // until the product is enqueued
     const uint8_t* as16 = a_scales;
     const uint8_t* bs16 = b_scales;
     if (M > 0 && N > 0 && K > 0) {
@@ -1717,7 +1720,7 @@ hipError_t launch_gemm_b32(BScale bmode, float amul, bool pm, float grid_d, int6
         const size_t abytes = (size_t)((M * kb16 + 255) / 256 * 256);
         const size_t bbytes = (size_t)(brows16 * kb16);
         void* ws = nullptr;
-        hipError_t e = stream_workspace(kWsScales, s, abytes + bbytes, &ws);
+        hipError_t e = held.take(kWsScales, s, abytes + bbytes, &ws);
         if (e != hipSuccess) return e;
         uint8_t* wa = static_cast<uint8_t*>(ws);
         uint8_t* wb = wa + abytes;

@@ -21,12 +21,29 @@ enum class ScaleKind : int { UE5M3 = 0, E4M3 = 1, E8M0 = 2 };
 // need and replaced by a larger one on demand (the replaced buffer is kept,
 // not freed, until the process ends): split-tile partials of the GEMMs,
 // block-32 scales expanded to the block-16 layout, per-workgroup partial
-// maxima of the amax kernels, scale codes in rows padded to 256 k.  Uses on one stream are ordered by the
-// stream, so a buffer is reused by the next call on that stream.  Returns
+// maxima of the amax kernels, scale codes in rows padded to 256 k.
+enum WorkspaceKind : int { kWsSplit = 0, kWsScales = 1, kWsAmax = 2, kWsPad = 3, kWsKinds = 4 };
+
+// One call's use of a workspace.  Uses on one stream are ordered by the
+// stream as long as each call's launches are enqueued together, so the
+// workspace is held, against other host threads on the same stream, from
+// take() to the end of this object's life: keep it until the last launch
+// that touches the buffer is enqueued.  A call that needs several kinds takes
+// them in the order kWsScales, kWsSplit, kWsPad.  take() returns
 // hipErrorStreamCaptureUnsupported when s is capturing and an allocation
 // would be needed.
-enum WorkspaceKind : int { kWsSplit = 0, kWsScales = 1, kWsAmax = 2, kWsPad = 3, kWsKinds = 4 };
-hipError_t stream_workspace(int kind, hipStream_t s, size_t bytes, void** out);
+struct WorkspaceSlot;
+class Workspace {
+  public:
+    Workspace() = default;
+    Workspace(const Workspace&) = delete;
+    Workspace& operator=(const Workspace&) = delete;
+    ~Workspace();
+    hipError_t take(int kind, hipStream_t s, size_t bytes, void** out);
+
+  private:
+    WorkspaceSlot* slot_ = nullptr;
+};
 
 // *amax_dev = max(clear ? 0 : *amax_dev, max |x|); a kept value must be a
 // non-negative finite float (the kernel takes an integer max of its bits).

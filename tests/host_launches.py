@@ -1,0 +1,68 @@
+"""Which kernels a library call launches, found on the host alone: builds
+host_launches.cpp (a double of the HIP runtime that records launches; 256
+compute units) and feeds it calls."""
+
+import functools
+import os
+import subprocess
+import tempfile
+
+import paper_2609_02846_amd as ue
+from paper_2609_02846_amd import build as ue_build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LAYOUTS = {"nt": 0, "nn": 1, "tn": 2}
+KINDS = {"ue5m3": 0, "e4m3": 1, "e8m0": 2}
+
+
+@functools.lru_cache(maxsize=None)
+def _recorder():
+    exe = os.path.join(tempfile.mkdtemp(prefix="host_launches_"), "host_launches")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-rdynamic", "-pthread",
+                           os.path.join(HERE, "host_launches.cpp"), "-o", exe, "-ldl"])
+    if not os.path.exists(ue.LIB_PATH):
+        ue_build.build(verbose=False)
+    return exe
+
+
+def _run(lines):
+    r = subprocess.run([_recorder(), ue.LIB_PATH], input="\n".join(lines) + "\n", capture_output=True, text=True,
+                       timeout=300)
+    assert r.returncode == 0, r.stderr
+    out = r.stdout.splitlines()
+    assert len(out) == len(lines)
+    return out
+
+
+def gemm_call(layout, M, N, K, entry="gemm", out="f32", fmt="ue5m3", block=16, tiled=None, stream=0, capturing=False):
+    """Command of one product under the layout's recipe blockings (tiled:
+    whether B has tile scales; by default as the layout's recipe)."""
+    colT = layout == "tn"
+    tiled = (not colT and fmt != "e8m0") if tiled is None else tiled
+    a = (1 if colT else 0) + (3 if block == 32 else 0)
+    b = (2 if tiled else 1 if layout != "nt" else 0) + (3 if block == 32 else 0)
+    if entry == "gemm" and (block == 32 or fmt != "ue5m3"):
+        entry = "ex"
+    return (f"gemm {entry} {LAYOUTS[layout]} {M} {N} {K} {a} {b} {1 if out == 'bf16' else 0} {KINDS[fmt]} {stream} "
+            f"{int(capturing)}")
+
+
+def amax_call(numel, stream=0, capturing=False):
+    return f"amax {numel} {stream} {int(capturing)}"
+
+
+def launches(calls):
+    """Per call: (status, [(kernel with template arguments, grid, block), ...]).
+    One process runs all of them in order (workspaces persist)."""
+    res = []
+    for line in _run(calls):
+        status, *rest = line.split(" | ")
+        res.append((int(status), [(r.rsplit(" ", 2)[0], *map(int, r.rsplit(" ", 2)[1:])) for r in rest]))
+    return res
+
+
+def together(threads, reps, call):
+    """The call from several host threads at once: (status, number of calls,
+    how many of them had another call's launch between their own)."""
+    w = _run([f"together {threads} {reps} {call}"])[0].split()
+    return int(w[0]), int(w[2]), int(w[4])

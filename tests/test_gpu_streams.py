@@ -11,6 +11,7 @@ eager run; the serial results themselves are checked against the oracle by
 the other GPU tests."""
 
 import ctypes
+import threading
 
 import pytest
 import torch
@@ -223,3 +224,29 @@ def _refused_during_capture(s):
     g.replay()
     torch.cuda.synchronize()
     assert torch.all(y == 1.0)
+
+
+def test_two_threads_on_one_stream_equal_serial():
+    """Two host threads running the sequence on the same stream (the library
+    call releases the interpreter lock): the workspaces they share must not
+    mix their calls up."""
+    say("two threads: serial reference")
+    ins = [_inputs(11), _inputs(12)]
+    ref, got = [_buffers(), _buffers()], [_buffers(), _buffers()]
+    for i in range(2):
+        _sequence(*ins[i], 200 + i, ref[i])
+    torch.cuda.synchronize()
+    say("two threads: at once")
+
+    def work(i):
+        for _ in range(8):
+            _sequence(*ins[i], 200 + i, got[i])
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for i in range(2):
+        _same(got[i], ref[i], f"thread {i}")

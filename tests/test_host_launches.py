@@ -1,0 +1,28 @@
+"""Host side of the library calls, without a device: what they launch and in
+what order (see host_launches.py)."""
+
+import pytest
+
+from tests.host_launches import amax_call, gemm_call, launches, together
+
+# Calls of several launches that pass data through a library workspace:
+# (what, call, launches)
+CHAINS = [
+    ("split tiles", gemm_call("nt", 4096, 4352, 1024), 2),
+    ("split tiles, E8M0", gemm_call("nt", 4096, 4352, 1024, fmt="e8m0", block=32), 2),
+    ("codes of blocks of 32", gemm_call("nt", 2048, 2048, 1024, block=32), 2),
+    ("codes of blocks of 32, then split tiles", gemm_call("nt", 4096, 4352, 1024, block=32), 3),
+    ("codes of blocks of 32, probe-matched", gemm_call("nt", 512, 512, 512, block=32, entry="pm"), 2),
+    ("scale codes padded for K, then split tiles", gemm_call("tn", 6144, 4096, 2000), 3),
+    ("partial maxima", amax_call(1 << 20), 2),
+]
+
+
+@pytest.mark.parametrize("what,call,n", CHAINS, ids=[c[0] for c in CHAINS])
+def test_calls_from_several_threads_keep_their_launches_together(what, call, n):
+    """Threads that share a stream share its workspaces: a call's launches
+    have to be enqueued with no other call's between them, or one would read
+    what the other wrote."""
+    status, kernels = launches([call])[0]
+    assert status == 0 and len(kernels) == n, kernels
+    assert together(4, 6, call) == (0, 24, 0)
