@@ -47,8 +47,8 @@ import functools
 
 import torch
 
-from . import (COL16T, COL32T, NN, NT, OUT_BF16, RN, ROW16, ROW32, SCALE_UE5M3, SR, TILE16, TILE32, TN, AmaxState,
-               _bf16_2d, _check, _dev_buf, _f32_out, _stream, amax_accumulate, load_library)
+from . import (COL16T, COL32T, NN, NT, OUT_BF16, RN, ROW16, ROW32, SCALE_UE5M3, TILE16, TILE32, TN, AmaxState,
+               _MODES, _bf16_2d, _check, _dev_buf, _f32_out, _stream, amax_accumulate, load_library)
 
 # The layer's small calls are bound by the host, so forward and backward
 # marshal the library calls themselves: all operands of a pass lie in one or
@@ -205,7 +205,7 @@ class _FP4LinearFn(torch.autograd.Function):
         dx = dw = None
         if not (need_dx or need_dw):
             return dx, dw, None, None, None
-        mode = SR if layer.grad_rounding == "sr" else RN
+        mode = _MODES[layer.grad_rounding]
         temp = _backward_layout(T, N, B, need_dx, need_dw)
         work = torch.empty(temp.bytes, dtype=torch.uint8, device=dy.device)
         t0 = work.data_ptr()
