@@ -1,7 +1,7 @@
 // Decoded-operand FP4 GEMM for few output rows (decoding and other small
 // batches): C[m, n] = alpha * sum_k A_hat[m, k] * B_hat[n, k] with M <= 64.
 // Same operands, decode and result contract as the kernels of gemm.hip; any
-// K % 16 == 0, any size of operand (64-bit addresses).
+// K % 16 == 0, any size of operand (64-bit addresses) with N < 2^29.
 //
 // Bound: reading B, the quantized weight, once (N K / 2 bytes).  A 256 x 256
 // output tile gives a weight of N rows only N / 256 workgroups that each walk
@@ -241,7 +241,8 @@ hipError_t launch_skinny_b(int64_t M, int64_t N, int64_t K, const uint8_t* a, co
 }  // namespace
 
 bool skinny_gemm(int64_t M, int64_t N, int64_t K) {
-    return M > 0 && M <= 64 && K > 0 && N > 0 && N < ((int64_t)1 << 34);
+    // a launch dimension holds less than 2^32 work-items: N / 32 workgroups of 256
+    return M > 0 && M <= 64 && K > 0 && N > 0 && N <= ((int64_t)1 << 29) - 32;
 }
 
 hipError_t launch_gemm_skinny(BScale bmode, float amul, int64_t M, int64_t N, int64_t K, const uint8_t* a,

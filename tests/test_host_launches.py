@@ -26,3 +26,14 @@ def test_calls_from_several_threads_keep_their_launches_together(what, call, n):
     status, kernels = launches([call])[0]
     assert status == 0 and len(kernels) == n, kernels
     assert together(4, 6, call) == (0, 24, 0)
+
+
+@pytest.mark.parametrize("N", [(1 << 29) - 48, (1 << 29) - 32, (1 << 29) - 16, 1 << 29, (1 << 32) + 16])
+@pytest.mark.parametrize("M", [1, 64])
+def test_few_rows_of_very_many_columns_launch(M, N):
+    """The streaming kernel takes 8 work-items per column, so that from 2^29
+    columns on it would not fit a launch dimension; the general kernel does."""
+    (status, kernels), = launches([gemm_call("nt", M, N, 16, out="bf16")])
+    assert status == 0
+    assert [k.split("<")[0] for k, _, _ in kernels] == ["gemm_fp4_skinny_kernel" if N <= (1 << 29) - 32
+                                                        else "gemm_fp4_kernel"]
