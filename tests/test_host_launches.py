@@ -28,7 +28,7 @@ def test_calls_from_several_threads_keep_their_launches_together(what, call, n):
     assert together(4, 6, call) == (0, 24, 0)
 
 
-@pytest.mark.parametrize("N", [(1 << 29) - 48, (1 << 29) - 32, (1 << 29) - 16, 1 << 29, (1 << 32) + 16])
+@pytest.mark.parametrize("N", [(1 << 29) - 48, (1 << 29) - 32, (1 << 29) - 16, 1 << 29, 1 << 31])
 @pytest.mark.parametrize("M", [1, 64])
 def test_few_rows_of_very_many_columns_launch(M, N):
     """The streaming kernel takes 8 work-items per column, so that from 2^29
