@@ -16,10 +16,8 @@
  *   allocates and frees them.  Every pointer must be 16-byte aligned.  The
  *   only memory the library allocates itself is a set of workspaces, one of
  *   each kind per (device, stream): the split-tile partials of ue5m3_gemm,
- *   the expanded block-32 scales of ue5m3_gemm_ex / ue5m3_gemm_pm, the
- *   padded scale codes of large products whose K is not a multiple of 256
- *   (a call that cannot have this one runs without it), and 16 KiB of
- *   per-workgroup partial maxima for the amax calls.  A workspace
+ *   the expanded block-32 scales of ue5m3_gemm_ex / ue5m3_gemm_pm, and
+ *   16 KiB of per-workgroup partial maxima for the amax calls.  A workspace
  *   is allocated (hipMalloc) by the first call on that pair that needs it,
  *   or needs a larger one; a replaced workspace is never freed before the
  *   process ends, so work already enqueued or captured in a graph keeps a
@@ -317,9 +315,8 @@ ue5m3_status_t ue5m3_gemm(ue5m3_layout_t layout, int64_t M, int64_t N, int64_t K
  * stream capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same arguments, checks, kernels, split plan and results (bit for bit) as
  * ue5m3_gemm; it calls no hipMalloc, hipFree or other allocating routine.
- * The split-tile partials (and the padded scale codes of a K that is not a
- * multiple of 256) go to a scratch array of 80 MiB that the library holds once
- * per device from the first call on that device until the process
+ * The split-tile partials go to a scratch array of 64 MiB that the library
+ * holds once per device from the first call on that device until the process
  * ends (its device address is looked up on that first call).  A call whose
  * split plan needs more than the array -- never on a device of at most 256
  * compute units, where the leftover tiles times their parts never exceed

@@ -14,10 +14,10 @@
 // Kernels of this file (gfx950, one 256-thread workgroup per CU, 256 x 256
 // output tiles, four waves of 128 x 128 in a 2 x 2 grid, 16
 // v_mfma_f32_32x32x16_f16 accumulators per wave = all 256 AccVGPRs):
-//  * operands and C below 2^31 bytes: gemm_fp4_reg_kernel (K % 256 == 0, or
-//    on scale codes copied to rows padded to it), persistent; packed FP4 rows and scale codes staged in LDS by direct
-//    loads four 64-k slices at a time, each wave decoding its own fragments
-//    in registers (no fp16 copy through LDS);
+//  * operands and C below 2^31 bytes: gemm_fp4_reg_kernel (any K), persistent;
+//    packed FP4 rows and scale codes staged in LDS by direct loads (the codes
+//    through registers where K % 256 != 0) four 64-k slices at a time, each
+//    wave decoding its own fragments in registers (no fp16 copy through LDS);
 //  * operands of 2^31 bytes and more (64-bit addresses): gemm_fp4_dma_kernel
 //    for K % 64 == 0, packed slices staged by direct loads and decoded once
 //    per workgroup into a double-buffered fp16 LDS stage, and
@@ -49,13 +49,11 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
-constexpr int BM = 256, BN = 256, BK = 64;
+constexpr int BK = 64;
 constexpr int kGemmThreads = 256;
 constexpr int LDSK = BK + 8;                         // padded LDS row, bf16 elements
 constexpr int kStageElems = (BM + BN) * LDSK;        // bf16 elements per stage
 constexpr int kSmemBytes = 2 * kStageElems * 2;
-constexpr int kXcds = 8;
-constexpr int kGroupM = 4;
 
 struct Frags {
     f16x8_t a[4], b[4];
@@ -623,13 +621,39 @@ struct SupSrc {
 // 128, position l % 8) and, with SC, its two scale loads (64 rows x 16 B).
 // Payload rows past the matrix fall outside the buffer and are dropped (they
 // only feed discarded outputs); scale rows are clamped when the tile is set up.
+// RAGK (K % 256 != 0): a scale row of kbt codes has no alignment and ends
+// inside the last stage, so the codes go through registers (load_codes) and
+// are stored to LDS during the stage before their own (put_codes).
+template <bool RAGK>
 struct SupLoader {
     i32x4_t pay, sca;        // payload and scale buffers of this wave's matrix (A or B)
     uint32_t rows8;          // bytes of 8 payload rows
     uint32_t ldp, lds;       // this wave's LDS offsets inside a payload / scale stage
+    const uint8_t* scp;      // RAGK: scale codes of this wave's matrix
+    uint32_t kbt;            // RAGK: codes per row, at least 16
+    uint4 c0, c1;            // RAGK: codes of rows lane and 64 + lane ...
+    uint32_t past;           // ... of which this many lead the stage's (the last stage)
+
+    // The 16 codes of stage G; in the last stage the row's last 16.
+    __device__ __forceinline__ void load_codes(const SupSrc& src, int64_t G) {
+        const uint32_t kb0 = (uint32_t)G * 16, at = min(kb0, kbt - 16);
+        past = kb0 - at;
+        __builtin_memcpy(&c0, scp + (src.so0 + at), 16);
+        __builtin_memcpy(&c1, scp + (src.so1 + at), 16);
+    }
+    // Those codes into the scale stage S, zeros past the row's end.
+    __device__ __forceinline__ void put_codes(uint8_t* S, int lane) {
+        if (past != 0) {
+            const uint32_t sh = 8 * past;
+            c0 = __builtin_bit_cast(uint4, __builtin_bit_cast(unsigned __int128, c0) >> sh);
+            c1 = __builtin_bit_cast(uint4, __builtin_bit_cast(unsigned __int128, c1) >> sh);
+        }
+        *reinterpret_cast<uint4*>(S + lds + lane * 16) = c0;
+        *reinterpret_cast<uint4*>(S + lds + 1024 + lane * 16) = c1;
+    }
 
     template <int I0, int I1, bool SC>
-    __device__ __forceinline__ void issue(uint32_t P, uint32_t S, const SupSrc& src, int64_t G) const {
+    __device__ __forceinline__ void issue(uint32_t P, uint32_t S, const SupSrc& src, int64_t G) {
         // the stage offset goes into the per-lane offset, which the buffer's
         // range check covers: the last row's stage may end past the row
         const uint32_t vo = src.off0 + (uint32_t)G * kSupRowBytes;
@@ -638,7 +662,9 @@ struct SupLoader {
             constexpr int i = decltype(ic)::value;
             dma_buf_x4<i * 1024>(pay, vo + i * rows8, 0u, pl);
         });
-        if (SC) {
+        if (SC && RAGK) {
+            load_codes(src, G);
+        } else if (SC) {
             const uint32_t gs = (uint32_t)G * 16;
             const uint32_t sl = S + lds;
             dma_buf_x4<0>(sca, src.so0, gs, sl);
@@ -657,22 +683,6 @@ struct SplitPlan {
     int parts;               // items per leftover tile (1: no split)
     float* part;             // [r][parts][4 waves][16 acc (i, j)][4 runs][64 lanes][4] fp32 partials
 };
-
-// Origin of logical tile t: workgroups are dispatched round-robin over the
-// XCDs, so logical tiles are remapped to give each XCD a contiguous range,
-// walked in groups of kGroupM tile rows (column-major inside a group) so
-// that tiles running together on one XCD share A and B rows in its L2.
-__device__ __forceinline__ void tile_origin(int t, int tiles_m, int tiles_n, int64_t& m0, int64_t& n0) {
-    const int ntiles = tiles_m * tiles_n;
-    if (ntiles % kXcds == 0) t = (t % kXcds) * (ntiles / kXcds) + t / kXcds;
-    const int group_tiles = kGroupM * tiles_n;
-    const int g = t / group_tiles;
-    const int first_m = g * kGroupM;
-    const int gm = min(tiles_m - first_m, kGroupM);
-    const int rr = t - g * group_tiles;
-    m0 = (int64_t)(first_m + rr % gm) * BM;
-    n0 = (int64_t)(rr / gm) * BN;
-}
 
 constexpr bool kStaggerSplit = true;
 
@@ -906,13 +916,15 @@ __device__ __forceinline__ void store_item(f32x16_t (&acc)[4][4], const WorkItem
 // must have an even number of stages when a workgroup runs more than one
 // (the stage buffers alternate and every item starts in buffer 0).  Sizes:
 // every operand, C and the partial workspace span less than 2^31 bytes.
-// K is a multiple of 256 and rowb the payload row's bytes: K / 2, or less
-// when the operands' K has been rounded up (launch_mode); the scale
-// codes past rowb are then 0, so what is staged past a row's end (the next
-// row's bytes, zeros past the matrix) counts as zeros.
-template <int BMODE, bool OUT_BF16, bool VEC>
+// RAGK: K % 256 != 0, K >= 256.  The last stage then runs past the rows' end;
+// its codes there are 0, so what is staged beside them (the next row's bytes,
+// zeros past the matrix) counts as zeros.  Codes copied to padded rows first
+// would need a workspace; they cost as much at the usual sizes (6144 x 4096 x
+// 2000 104 us, in place 100) and up to 2.4% less where the rows' codes have no
+// alignment and K is long (9728 x 16960 x 7248: 1821 and 1866).
+template <int BMODE, bool OUT_BF16, bool VEC, bool RAGK>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_reg_kernel(
-    int M, int N, int K, uint32_t rowb, int tiles_m, int tiles_n, int items, SplitPlan sp,
+    int M, int N, int K, int tiles_m, int tiles_n, int items, SplitPlan sp,
     const uint8_t* __restrict__ A, const uint8_t* __restrict__ As, const float* __restrict__ a_dec,
     const uint8_t* __restrict__ B, const uint8_t* __restrict__ Bs, const float* __restrict__ b_dec,
     void* __restrict__ C, float amul) {
@@ -929,15 +941,21 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_reg_kernel(
     const int r = lane & 31, hi = lane >> 5;
 
     const int kbt = K / 16;                          // scale bytes per row
-    const int NG = K / (kSupK * BK);                 // stages of a whole tile
+    const int NG = (K + kSupK * BK - 1) / (kSupK * BK);   // stages of a whole tile
+    const uint32_t rowb = (uint32_t)(K / 2);         // payload bytes per row
 
     // Loads: waves 0, 1 bring A stage rows 0..255, waves 2, 3 B rows 256..511.
     const bool isA = wave < 2;
     const int xw = 128 * (wave & 1);                 // first stage row of the wave within A or B
     const int brows = BMODE == (int)BScale::Row ? N : (N + 15) / 16;   // rows of the B scale matrix
-    SupLoader L;
+    SupLoader<RAGK> L;
     L.pay = isA ? buffer_rsrc(A, (uint32_t)M * rowb) : buffer_rsrc(B, (uint32_t)N * rowb);
-    L.sca = isA ? buffer_rsrc(As, (uint32_t)M * kbt) : buffer_rsrc(Bs, (uint32_t)brows * kbt);
+    if (RAGK) {
+        L.scp = isA ? As : Bs;
+        L.kbt = (uint32_t)kbt;
+    } else {
+        L.sca = isA ? buffer_rsrc(As, (uint32_t)M * kbt) : buffer_rsrc(Bs, (uint32_t)brows * kbt);
+    }
     L.rows8 = 8 * rowb;
     L.ldp = (uint32_t)(128 * wave * kSupRowBytes);
     L.lds = (uint32_t)(128 * wave * kSupK * 4);
@@ -989,9 +1007,13 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_reg_kernel(
     {
         const WorkItem w = work_item(item_at(0), sp, NG);
         const SupSrc q = src_of(w.t);
-        L.issue<0, kSupPayLoads, true>(P0, S0, q, w.g0);
-        L.issue<0, kSupPayLoads, true>(P1, S1, q, min(w.g0 + 1, w.g1 - 1));
-        wait_vmem<kSupLoads>();
+        L.template issue<0, kSupPayLoads, true>(P0, S0, q, w.g0);
+        if (RAGK) {
+            wait_vmem<0>();
+            L.put_codes(sC0, lane);
+        }
+        L.template issue<0, kSupPayLoads, true>(P1, S1, q, min(w.g0 + 1, w.g1 - 1));
+        if (!RAGK) wait_vmem<kSupLoads>();
         __syncthreads();
     }
 
@@ -1022,7 +1044,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_reg_kernel(
             q.off0 = in_cur ? scur.off0 : snxt.off0;
             q.so0 = in_cur ? scur.so0 : snxt.so0;
             q.so1 = in_cur ? scur.so1 : snxt.so1;
-            L.issue<I0v, I1v, SCv>(ldP, ldS, q, Gl);
+            L.template issue<I0v, I1v, SCv>(ldP, ldS, q, Gl);
         };
 
 #pragma unroll
@@ -1051,6 +1073,9 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_reg_kernel(
             using CP = std::integral_constant<int, kSupPayLoads>;
             using F = std::integral_constant<bool, false>;
             using T = std::integral_constant<bool, true>;
+            // the next stage's codes: their buffer was last read before the
+            // barrier in the previous stage's slice 3
+            if (RAGK && SL == 3) L.put_codes(const_cast<uint8_t*>(Sn), lane);
             decode_kstep<1>(F1, Rc, sel);
             mfma16_t(acc, F0);
             kstep_schedule<0, 0, 5>();
@@ -1411,43 +1436,39 @@ hipError_t split_workspace(Workspace& ws, hipStream_t s, size_t part_floats, flo
     return e;
 }
 
-// Scale codes of one operand copied to the layout a kernel reads: out row r
-// (of rows) holds, at column c < cols, code c >> shift of input row r / rrep,
-// and zeros up to its stride.
+// Scale codes of one operand with blocks of 32 in the block-16 layout: out
+// row r (of rows) holds at column c < cols code c / 2 of input row r / rrep.
 struct ScaleCopy {
     const uint8_t* in;
     uint8_t* out;
-    int64_t rows, cols, stride, cols_in;
-    int shift, rrep;
+    int64_t rows, cols;
+    int rrep;
 };
 
 // Both operands' scale codes in one launch: the first `a_blocks` workgroups
 // walk A, the others B.  Latency-bound (a few MB at most; two launches of a
 // byte per thread took 5 and 3 us for 4096 x 4096 operands): 4 codes per
-// thread where the row stride allows it.
+// thread where the row length allows it.
 __global__ __launch_bounds__(256) void copy_scales_kernel(ScaleCopy a, ScaleCopy b, int a_blocks) {
     const bool is_a = (int)blockIdx.x < a_blocks;
     const ScaleCopy s = is_a ? a : b;
     const int64_t first = (int64_t)(is_a ? blockIdx.x : blockIdx.x - a_blocks) * 256 + threadIdx.x;
     const int64_t step = (int64_t)(is_a ? a_blocks : gridDim.x - a_blocks) * 256;
-    auto code = [&](int64_t r, int64_t c) -> uint32_t {
-        return c < s.cols ? s.in[(r / s.rrep) * s.cols_in + (c >> s.shift)] : 0u;
-    };
-    if ((s.stride & 3) == 0) {
-        const uint32_t per = (uint32_t)(s.stride >> 2);
+    auto code = [&](int64_t r, int64_t c) -> uint32_t { return s.in[(r / s.rrep) * (s.cols / 2) + (c >> 1)]; };
+    if ((s.cols & 3) == 0) {
+        const uint32_t per = (uint32_t)(s.cols >> 2);
         for (int64_t i = first; i < s.rows * per; i += step) {
             const int64_t r = i / per, c = 4 * (i - r * per);
             reinterpret_cast<uint32_t*>(s.out)[i] =
                 code(r, c) | code(r, c + 1) << 8 | code(r, c + 2) << 16 | code(r, c + 3) << 24;
         }
     } else {
-        for (int64_t i = first; i < s.rows * s.stride; i += step)
-            s.out[i] = (uint8_t)code(i / s.stride, i % s.stride);
+        for (int64_t i = first; i < s.rows * s.cols; i += step) s.out[i] = (uint8_t)code(i / s.cols, i % s.cols);
     }
 }
 
 hipError_t copy_scales(const ScaleCopy& a, const ScaleCopy& b, hipStream_t s) {
-    auto blocks = [](const ScaleCopy& c) { return (int)min(max((c.rows * c.stride / 4 + 255) / 256, (int64_t)1), (int64_t)2048); };
+    auto blocks = [](const ScaleCopy& c) { return (int)min(max((c.rows * c.cols / 4 + 255) / 256, (int64_t)1), (int64_t)2048); };
     const int na = blocks(a), nb = blocks(b);
     hipLaunchKernelGGL(copy_scales_kernel, dim3((unsigned)(na + nb)), dim3(256), 0, s, a, b, na);
     return hipGetLastError();
@@ -1465,9 +1486,10 @@ bool vector_epilogue(int64_t N, int tiles_m) {
     return N % 4 == 0;
 }
 
-// Floats of split-tile partials that launch_reg's plan needs.
+// How launch_reg runs a product's tiles.  floats: split-tile partials.
 struct RegPlan {
     int tiles_m, tiles_n, T, rem, parts;             // rem tiles split into parts (parts > 1)
+    int tail;                                        // leftover tiles that run as small tiles
     size_t floats;
 };
 
@@ -1478,40 +1500,51 @@ RegPlan reg_plan(int64_t M, int64_t N, int64_t K, int cus) {
     p.T = p.tiles_m * p.tiles_n;
     p.rem = p.T % cus;
     p.parts = 1;
+    p.tail = 0;
     p.floats = 0;
-    const int NG = (int)(K / (kSupK * BK));
+    const int NG = (int)((K + kSupK * BK - 1) / (kSupK * BK));
     // One workgroup per CU at a time (LDS-bound).  Split only a partial last
     // wave of tiles that leaves at least 1 - 1/kSplitRemDiv of the CUs idle;
-    // parts cover whole stage pairs when the stage count is even.
+    // parts cover whole stage pairs when the stage count is even.  A product
+    // with K % 256 != 0 takes no workspace, so that it runs, with the same
+    // result, on a capturing stream that has none: its leftover tiles run as
+    // smaller tiles instead (21504 x 4096 x 7888, 64 left over: 1054 us, as
+    // whole tiles 1120; split along K it took 1041, 4352 x 4096 x 4080 with 16
+    // left over 124 both ways, 6144 x 4096 x 8000 with 128 333 and 320).
     if (p.T > cus && p.rem > 0 && p.rem <= cus / kSplitRemDiv) {
+        if (K % (kSupK * BK) != 0) {
+            p.tail = p.rem;
+            return p;
+        }
         p.parts = min(cus / p.rem, NG % 2 == 0 ? NG / 2 : NG);
         if (p.parts > 1) p.floats = (size_t)p.rem * p.parts * 65536;
     }
     return p;
 }
 
-// K: a multiple of 256 (rounded up when the payload rows of rowb bytes are
-// shorter); part: room for the plan's partials.
-template <int BMODE, bool OUT_BF16>
-hipError_t launch_reg(const RegPlan& p, int cus, float* part, int64_t M, int64_t N, int64_t K, uint32_t rowb,
-                      const uint8_t* a, const uint8_t* as, const float* ad, const uint8_t* b, const uint8_t* bs,
+// part: room for the plan's partials.
+template <int BMODE, bool OUT_BF16, bool RAGK>
+hipError_t launch_reg(const RegPlan& p, int cus, float* part, int64_t M, int64_t N, int64_t K, const uint8_t* a, const uint8_t* as, const float* ad, const uint8_t* b, const uint8_t* bs,
                       const float* bd, void* c, float amul, hipStream_t s) {
-    const int NG = (int)(K / (kSupK * BK));
-    SplitPlan sp{p.T, 1, nullptr};
+    const int NG = (int)((K + kSupK * BK - 1) / (kSupK * BK));
+    SplitPlan sp{p.T - p.tail, 1, nullptr};
     if (p.parts > 1) sp = SplitPlan{p.T - p.rem, p.parts, part};
-    const int items = sp.Tdp + (p.T - sp.Tdp) * sp.parts;
+    const int items = sp.Tdp + (p.T - p.tail - sp.Tdp) * sp.parts;
     // persistent (one workgroup per CU walking the items) when every item has
     // an even stage count, else one item per workgroup
     const int grid = NG % 2 == 0 ? min(items, cus) : items;
     if (vector_epilogue<OUT_BF16>(N, p.tiles_m))
-        hipLaunchKernelGGL((gemm_fp4_reg_kernel<BMODE, OUT_BF16, true>), dim3((unsigned)grid), dim3(kGemmThreads),
-                           0, s, (int)M, (int)N, (int)K, rowb, p.tiles_m, p.tiles_n, items, sp, a, as, ad, b, bs, bd,
+        hipLaunchKernelGGL((gemm_fp4_reg_kernel<BMODE, OUT_BF16, true, RAGK>), dim3((unsigned)grid), dim3(kGemmThreads),
+                           0, s, (int)M, (int)N, (int)K, p.tiles_m, p.tiles_n, items, sp, a, as, ad, b, bs, bd,
                            c, amul);
     else
-        hipLaunchKernelGGL((gemm_fp4_reg_kernel<BMODE, OUT_BF16, false>), dim3((unsigned)grid), dim3(kGemmThreads),
-                           0, s, (int)M, (int)N, (int)K, rowb, p.tiles_m, p.tiles_n, items, sp, a, as, ad, b, bs, bd,
+        hipLaunchKernelGGL((gemm_fp4_reg_kernel<BMODE, OUT_BF16, false, RAGK>), dim3((unsigned)grid), dim3(kGemmThreads),
+                           0, s, (int)M, (int)N, (int)K, p.tiles_m, p.tiles_n, items, sp, a, as, ad, b, bs, bd,
                            c, amul);
     hipError_t e = hipGetLastError();
+    if (e == hipSuccess && p.tail > 0)
+        return launch_gemm_mid_tail((BScale)BMODE, amul, M, N, K, cus, p.T - p.tail, a, as, ad, b, bs, bd, c, OUT_BF16,
+                                    s);
     if (e != hipSuccess || sp.parts == 1) return e;
     hipLaunchKernelGGL((gemm_split_sum_kernel<BMODE, OUT_BF16>), dim3((unsigned)(64 * (p.T - sp.Tdp))), dim3(256),
                        0, s, M, N, p.tiles_m, p.tiles_n, sp, ad, bd, c, amul);
@@ -1599,23 +1632,25 @@ hipError_t device_cus(int* cus) {
 // 6144 x 4096 (192 tiles) 87 / 84, where the small tiles model 93 and take
 // 95; 4096 x 4096 x 4096 (256) 100 / 102, small 122 / 125; 2000 x 4096 x
 // 6144 (128) 107 / 109, small 91 / 97; 777 x 4096 x 21504 (64) 357 / 352,
-// small 153 / 151.
+// small 153 / 151.  A stage is 256 k whether or not K fills the last one.
+// K % 256 != 0: the leftover tiles run as smaller ones (reg_plan), and an odd
+// stage count, whose items are not persistent, costs some 3 us per round
+// (8192 x 8192 x 528: 102 us, small tiles 86; 4096 x 4096 x 2064: 62 and 71).
 double reg_time(int64_t M, int64_t N, int64_t K, int cus) {
     const int64_t T = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
     const int64_t full = T / cus, rem = T % cus;
     const double share = T >= cus ? 1.0 : (double)rem / cus;
-    const double round = 4.0 + 1e-3 * K * (16.3 + (share > 0.5 ? 13.0 * (share - 0.5) : 0.0));
+    const int64_t stages = (K + 255) / 256;
+    const bool whole = K % 256 == 0;
+    const double fixed = whole || stages % 2 == 0 ? 4.0 : 7.0;
+    const double round = fixed + 0.256 * stages * (16.3 + (share > 0.5 ? 13.0 * (share - 0.5) : 0.0));
     double t = 3.0 + full * round;
-    if (rem > 0) t += (full > 0 && rem <= cus / kSplitRemDiv) ? round * rem / cus + 15.0 : round;
+    if (rem > 0 && full > 0 && rem <= cus / kSplitRemDiv)
+        t += whole ? round * rem / cus + 15.0 : mid_tail_time(K, rem, cus);
+    else if (rem > 0)
+        t += round;
     return t;
 }
-
-// K not a multiple of 256 runs in 256 x 256 tiles on scale codes copied to
-// rows padded with zeros: the copy and its launch, us.  Measured, padded large
-// tiles / small tiles, us: 21504 x 4096 x 7888 1029 / 1271, 6144 x 4096 x 8000
-// 315 / 365, 4096 x 4096 x 4000 112 / 138, 4096 x 4096 x 2064 66 / 73; with few
-// k the small ones stay ahead: 6144 x 4096 x 1040 80 / 59.
-constexpr double kPadUs = 6.0;
 
 template <int BMODE>
 hipError_t launch_mode(int64_t M, int64_t N, int64_t K, const uint8_t* a, const uint8_t* as,
@@ -1625,57 +1660,32 @@ hipError_t launch_mode(int64_t M, int64_t N, int64_t K, const uint8_t* a, const 
     // C) with 32-bit offsets
     const int64_t kLim = (int64_t)1 << 31;
     const int64_t Kp = (K + 255) / 256 * 256;
-    const bool reg = K > 0 && M * (Kp / 2) < kLim && N * (Kp / 2) < kLim && M * N * 4 < kLim;
+    const bool reg = K >= 256 && M * (Kp / 2) < kLim && N * (Kp / 2) < kLim && M * N * 4 < kLim;
     const bool mid = mid_gemm_fits(M, N, K);
     if (reg || mid) {
         int cus = 0;
         hipError_t e = device_cus(&cus);
         if (e != hipSuccess) return e;
-        // the cost of K % 256: copying the scale codes to padded rows
-        const bool padded = K % 256 != 0;
-        const bool use_mid = mid && (!reg || mid_gemm_time(M, N, K, cus) <
-                                                 reg_time(M, N, Kp, cus) + (padded ? kPadUs : 0.0));
-        if (reg && !use_mid) {
-            const RegPlan p = reg_plan(M, N, Kp, cus);
-            const uint8_t *as16 = as, *bs16 = bs;
-            const int64_t kb = K / 16, kp = Kp / 16;
-            const int64_t brows = BMODE == (int)BScale::Row ? N : (N + 15) / 16;
-            const size_t abytes = padded ? (size_t)((M * kp + 255) / 256 * 256) : 0;
-            const size_t bbytes = padded ? (size_t)(brows * kp) : 0;
-            const size_t pad_at = (p.floats + 63) / 64 * 64;     // fixed buffer: partials, then padded codes
-            const size_t need = pad_at * sizeof(float) + abytes + bbytes;
-            Workspace split_ws, pad_ws;              // held until the launches are enqueued
-            float* part = nullptr;
-            uint8_t* pad = nullptr;
-            if (fx != nullptr) {
-                e = need <= fx->floats * sizeof(float) ? hipSuccess : hipErrorOutOfMemory;
-                part = fx->part;
-                pad = reinterpret_cast<uint8_t*>(fx->part + pad_at);
-            } else if (!padded || need <= kNoallocBytes) {
-                if (p.floats > 0) e = split_workspace(split_ws, s, p.floats, &part);
-                void* ws = nullptr;
-                if (e == hipSuccess && padded) e = pad_ws.take(kWsPad, s, abytes + bbytes, &ws);
-                pad = static_cast<uint8_t*>(ws);
-            } else {
-                e = hipErrorOutOfMemory;             // as with the fixed buffer, so that both take the same way
-            }
-            if (e == hipSuccess && padded) {
-                e = copy_scales({as, pad, M, kb, kp, kb, 0, 1}, {bs, pad + abytes, brows, kb, kp, kb, 0, 1}, s);
-                if (e != hipSuccess) return e;
-                as16 = pad;
-                bs16 = pad + abytes;
-            }
-            if (e == hipSuccess)
-                return c_bf16 ? launch_reg<BMODE, true>(p, cus, part, M, N, Kp, (uint32_t)(K / 2), a, as16, ad, b, bs16,
-                                                        bd, c, amul, s)
-                              : launch_reg<BMODE, false>(p, cus, part, M, N, Kp, (uint32_t)(K / 2), a, as16, ad, b,
-                                                         bs16, bd, c, amul, s);
-            // No workspace (a capturing stream that has none yet, no slot, no
-            // memory): K % 256 == 0 refuses; a padded call goes on without one.
-            if (!padded) return e;
-            (void)hipGetLastError();
+        if (mid && (!reg || mid_gemm_time(M, N, K, cus) < reg_time(M, N, K, cus)))
+            return launch_gemm_mid((BScale)BMODE, amul, M, N, K, cus, a, as, ad, b, bs, bd, c, c_bf16, s);
+        const RegPlan p = reg_plan(M, N, K, cus);
+        if (K % (kSupK * BK) != 0) {
+            // (the dgrad product's own instantiation only serves profiles of K % 256 == 0)
+            constexpr int BM2 = BMODE == (int)BScale::Row ? (int)BScale::Row : (int)BScale::Tile;
+            return c_bf16 ? launch_reg<BM2, true, true>(p, cus, nullptr, M, N, K, a, as, ad, b, bs, bd, c, amul, s)
+                          : launch_reg<BM2, false, true>(p, cus, nullptr, M, N, K, a, as, ad, b, bs, bd, c, amul, s);
         }
-        if (mid) return launch_gemm_mid((BScale)BMODE, amul, M, N, K, cus, a, as, ad, b, bs, bd, c, c_bf16, s);
+        Workspace held;                              // until the sum is enqueued
+        float* part = nullptr;
+        if (fx != nullptr) {
+            if (p.floats > fx->floats) return hipErrorOutOfMemory;
+            part = fx->part;
+        } else if (p.floats > 0) {
+            e = split_workspace(held, s, p.floats, &part);
+            if (e != hipSuccess) return e;
+        }
+        return c_bf16 ? launch_reg<BMODE, true, false>(p, cus, part, M, N, K, a, as, ad, b, bs, bd, c, amul, s)
+                      : launch_reg<BMODE, false, false>(p, cus, part, M, N, K, a, as, ad, b, bs, bd, c, amul, s);
     }
     if (K % BK == 0 && K > 0)
         return c_bf16 ? launch_dma<BMODE, true>(M, N, K, a, as, ad, b, bs, bd, c, amul, s)
@@ -1715,7 +1725,7 @@ hipError_t launch_gemm_b32(BScale bmode, float amul, bool pm, float grid_d, int6
     const uint8_t* bs16 = b_scales;
     if (M > 0 && N > 0 && K > 0) {
         const bool tiled = bmode != BScale::Row;
-        const int64_t kb16 = K / 16, kb32 = K / 32;
+        const int64_t kb16 = K / 16;
         const int64_t brows16 = tiled ? N / 16 : N;
         const size_t abytes = (size_t)((M * kb16 + 255) / 256 * 256);
         const size_t bbytes = (size_t)(brows16 * kb16);
@@ -1726,8 +1736,7 @@ hipError_t launch_gemm_b32(BScale bmode, float amul, bool pm, float grid_d, int6
         uint8_t* wb = wa + abytes;
         // block-32 codes to the block-16 layout: each code twice along k, and
         // each 32 x 32 tile row as two 16-row tile rows
-        e = copy_scales({a_scales, wa, M, kb16, kb16, kb32, 1, 1},
-                        {b_scales, wb, brows16, kb16, kb16, kb32, 1, tiled ? 2 : 1}, s);
+        e = copy_scales({a_scales, wa, M, kb16, 1}, {b_scales, wb, brows16, kb16, tiled ? 2 : 1}, s);
         if (e != hipSuccess) return e;
         as16 = wa;
         bs16 = wb;

@@ -1,6 +1,7 @@
 // Decoded-operand FP4 GEMM in tiles of 64 or 128 rows and columns, any
 // K % 16 == 0: the calls whose 256 x 256 tiles (gemm_fp4_reg_kernel) would
-// leave most CUs idle or whose K is not a multiple of 256.
+// leave most CUs idle, and the leftover tiles of large products whose K is
+// not a multiple of 256 (reg_plan).
 //
 // The decode is the register decode of gemm_fp4_reg_kernel: the packed rows
 // and their scale codes are staged in LDS 256 k at a time, double buffered,
@@ -16,8 +17,7 @@
 // large ones leave CUs without work (mid_plan, reg_time).  Measured against
 // the kernels that ran before, us: 300 x 4096 x 4096 72 -> 22, 777 x 4096 x
 // 21504 352 -> 151, dgrad 2000 x 4096 x 6144 109 -> 97; K not a multiple of
-// 256: 6144 x 4096 x 2000 230 -> 111, 1520 x 1360 x 3408 178 -> 29, 1520 x
-// 3408 x 1360 71 -> 26.
+// 256: 1520 x 1360 x 3408 178 -> 29, 1520 x 3408 x 1360 71 -> 26.
 #include "codec.hpp"
 #include "fp4_decode.hpp"
 #include "gemm_regs.hpp"
@@ -110,7 +110,7 @@ __device__ __forceinline__ uint4 mid_scales(const uint8_t* __restrict__ row, int
 
 template <int BMODE, int TM, int TN, int KS, bool OUT_BF16>
 __global__ __launch_bounds__(256 * KS, KS == 1 ? 2 : 1) void gemm_fp4_mid_kernel(
-    int M, int N, int K, int tiles_m, int tiles_n, const uint8_t* __restrict__ A, const uint8_t* __restrict__ As,
+    int M, int N, int K, int tiles_m, int tiles_n, int tail, const uint8_t* __restrict__ A, const uint8_t* __restrict__ As,
     const float* __restrict__ a_dec, const uint8_t* __restrict__ B, const uint8_t* __restrict__ Bs,
     const float* __restrict__ b_dec, void* __restrict__ C, float amul) {
     constexpr int G = TM + TN;
@@ -129,7 +129,17 @@ __global__ __launch_bounds__(256 * KS, KS == 1 ? 2 : 1) void gemm_fp4_mid_kernel
     uint8_t* const buf1 = buf0 + kStage;
 
     int64_t m0, n0;
-    mid_origin(blockIdx.x, tiles_m, tiles_n, 64 * TM, 64 * TN, m0, n0);
+    if (tail < 0) {
+        mid_origin(blockIdx.x, tiles_m, tiles_n, 64 * TM, 64 * TN, m0, n0);
+    } else {
+        // the large tiles from `tail` on (tiles_m x tiles_n of them), in pieces
+        constexpr int kPieces = (BN / (64 * TN)) * (BM / (64 * TM));
+        const int q = blockIdx.x % kPieces;
+        tile_origin(tail + blockIdx.x / kPieces, tiles_m, tiles_n, m0, n0);
+        m0 += q / (BN / (64 * TN)) * 64 * TM;
+        n0 += q % (BN / (64 * TN)) * 64 * TN;
+        if (m0 >= M || n0 >= N) return;              // the whole workgroup
+    }
 
     const int kbt = K / 16;
     const int slices = (kbt + 3) / 4, stages = (kbt + kMidSc - 1) / kMidSc;
@@ -369,27 +379,24 @@ __global__ __launch_bounds__(256 * KS, KS == 1 ? 2 : 1) void gemm_fp4_mid_kernel
 }
 
 template <int BMODE, int TM, int TN, int KS>
-hipError_t launch_mid_t(int64_t M, int64_t N, int64_t K, const uint8_t* a, const uint8_t* as, const float* ad,
-                        const uint8_t* b, const uint8_t* bs, const float* bd, void* c, bool c_bf16, float amul,
-                        hipStream_t s) {
-    const int tm = (int)((M + 64 * TM - 1) / (64 * TM)), tn = (int)((N + 64 * TN - 1) / (64 * TN));
+hipError_t launch_mid_t(int blocks, int tiles_m, int tiles_n, int tail, int64_t M, int64_t N, int64_t K, const uint8_t* a,
+                        const uint8_t* as, const float* ad, const uint8_t* b, const uint8_t* bs, const float* bd, void* c,
+                        bool c_bf16, float amul, hipStream_t s) {
     if (c_bf16)
-        hipLaunchKernelGGL((gemm_fp4_mid_kernel<BMODE, TM, TN, KS, true>), dim3((unsigned)(tm * tn)), dim3(256 * KS),
-                           0, s, (int)M, (int)N, (int)K, tm, tn, a, as, ad, b, bs, bd, c, amul);
+        hipLaunchKernelGGL((gemm_fp4_mid_kernel<BMODE, TM, TN, KS, true>), dim3((unsigned)blocks), dim3(256 * KS), 0, s,
+                           (int)M, (int)N, (int)K, tiles_m, tiles_n, tail, a, as, ad, b, bs, bd, c, amul);
     else
-        hipLaunchKernelGGL((gemm_fp4_mid_kernel<BMODE, TM, TN, KS, false>), dim3((unsigned)(tm * tn)), dim3(256 * KS),
-                           0, s, (int)M, (int)N, (int)K, tm, tn, a, as, ad, b, bs, bd, c, amul);
+        hipLaunchKernelGGL((gemm_fp4_mid_kernel<BMODE, TM, TN, KS, false>), dim3((unsigned)blocks), dim3(256 * KS), 0, s,
+                           (int)M, (int)N, (int)K, tiles_m, tiles_n, tail, a, as, ad, b, bs, bd, c, amul);
     return hipGetLastError();
 }
 
 // Modelled time (us) of one configuration: the busiest CU runs `per` tiles,
 // each with a fixed part (prologue, epilogue) and tau ns per k.
-double mid_time(int64_t M, int64_t N, int64_t K, int cus, int bm, int bn, double fixed, double tau, double tau1) {
-    const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+double mid_time(int64_t tiles, int64_t K, int cus, double fixed, double tau, double tau1) {
     const int64_t per = (tiles + cus - 1) / cus;
     return 3.0 + per * (fixed + 1e-3 * K * (per == 1 ? tau1 : tau));
 }
-
 struct MidPlan {
     int tm, tn, ks;
     double us;
@@ -402,14 +409,12 @@ struct MidPlan {
 // 17 / 15.5, 1520 x 1360 x 3408 2x2x2 30 / 29, 1520 x 3408 x 1360 2x2x1
 // 27 / 26, 6144 x 4096 x 8000 2x2x1 361 / 365.  Two K groups (ks = 2) help a CU that has only one tile: with one
 // wave per SIMD its decode and products do not overlap fully.
-MidPlan mid_plan(int64_t M, int64_t N, int64_t K, int cus) {
+template <typename Tiles>
+MidPlan mid_plan(Tiles tiles, int64_t K, int cus) {
     const MidPlan c[6] = {
-        {2, 2, 1, mid_time(M, N, K, cus, 128, 128, 2.0, 7.2, 7.6)},
-        {2, 2, 2, mid_time(M, N, K, cus, 128, 128, 3.5, 7.2, 6.8)},
-        {1, 2, 1, mid_time(M, N, K, cus, 64, 128, 1.7, 4.6, 5.1)},
-        {1, 2, 2, mid_time(M, N, K, cus, 64, 128, 2.8, 4.6, 4.2)},
-        {1, 1, 1, mid_time(M, N, K, cus, 64, 64, 1.0, 2.9, 3.4)},
-        {1, 1, 2, mid_time(M, N, K, cus, 64, 64, 2.0, 2.9, 2.8)},
+        {2, 2, 1, mid_time(tiles(2, 2), K, cus, 2.0, 7.2, 7.6)}, {2, 2, 2, mid_time(tiles(2, 2), K, cus, 3.5, 7.2, 6.8)},
+        {1, 2, 1, mid_time(tiles(1, 2), K, cus, 1.7, 4.6, 5.1)}, {1, 2, 2, mid_time(tiles(1, 2), K, cus, 2.8, 4.6, 4.2)},
+        {1, 1, 1, mid_time(tiles(1, 1), K, cus, 1.0, 2.9, 3.4)}, {1, 1, 2, mid_time(tiles(1, 1), K, cus, 2.0, 2.9, 2.8)},
     };
     MidPlan best = c[0];
     for (int i = 1; i < 6; ++i)
@@ -417,16 +422,30 @@ MidPlan mid_plan(int64_t M, int64_t N, int64_t K, int cus) {
     return best;
 }
 
+// The whole product; `large` tiles of 256 x 256 cut into smaller ones.
+MidPlan mid_plan(int64_t M, int64_t N, int64_t K, int cus) {
+    return mid_plan([=](int tm, int tn) { return ((M + 64 * tm - 1) / (64 * tm)) * ((N + 64 * tn - 1) / (64 * tn)); }, K,
+                    cus);
+}
+MidPlan mid_tail_plan(int64_t K, int64_t large, int cus) {
+    return mid_plan([=](int tm, int tn) { return large * (BM / (64 * tm)) * (BN / (64 * tn)); }, K, cus);
+}
+
+// tail < 0: the whole product; otherwise its large tiles from `tail` on.
 template <int BMODE>
-hipError_t launch_mid_b(const MidPlan& p, int64_t M, int64_t N, int64_t K, const uint8_t* a, const uint8_t* as,
+hipError_t launch_mid_b(const MidPlan& p, int tail, int64_t M, int64_t N, int64_t K, const uint8_t* a, const uint8_t* as,
                         const float* ad, const uint8_t* b, const uint8_t* bs, const float* bd, void* c, bool c_bf16,
                         float amul, hipStream_t s) {
-#define UE5M3_MID(TM, TN) (p.ks == 1 ? launch_mid_t<BMODE, TM, TN, 1>(M, N, K, a, as, ad, b, bs, bd, c, c_bf16, amul, s) \
-                                     : launch_mid_t<BMODE, TM, TN, 2>(M, N, K, a, as, ad, b, bs, bd, c, c_bf16, amul, s))
+    const int bm = tail < 0 ? 64 * p.tm : BM, bn = tail < 0 ? 64 * p.tn : BN;
+    const int tm = (int)((M + bm - 1) / bm), tn = (int)((N + bn - 1) / bn);
+    const int blocks = tail < 0 ? tm * tn : (tm * tn - tail) * (BM / (64 * p.tm)) * (BN / (64 * p.tn));
+#define UE5M3_MID_ARGS (blocks, tm, tn, tail, M, N, K, a, as, ad, b, bs, bd, c, c_bf16, amul, s)
+#define UE5M3_MID(TM, TN) (p.ks == 1 ? launch_mid_t<BMODE, TM, TN, 1> UE5M3_MID_ARGS : launch_mid_t<BMODE, TM, TN, 2> UE5M3_MID_ARGS)
     if (p.tm == 2) return UE5M3_MID(2, 2);
     if (p.tn == 2) return UE5M3_MID(1, 2);
     return UE5M3_MID(1, 1);
 #undef UE5M3_MID
+#undef UE5M3_MID_ARGS
 }
 
 }  // namespace
@@ -444,9 +463,24 @@ hipError_t launch_gemm_mid(BScale bmode, float amul, int64_t M, int64_t N, int64
                            const float* b_dec, void* c, bool c_bf16, hipStream_t s) {
     const MidPlan p = mid_plan(M, N, K, cus);
     return bmode == BScale::Row
-               ? launch_mid_b<(int)BScale::Row>(p, M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16, amul, s)
-               : launch_mid_b<(int)BScale::Tile>(p, M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16, amul,
-                                                 s);
+               ? launch_mid_b<(int)BScale::Row>(p, -1, M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16, amul,
+                                                s)
+               : launch_mid_b<(int)BScale::Tile>(p, -1, M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16,
+                                                 amul, s);
+}
+
+double mid_tail_time(int64_t K, int64_t large, int cus) { return mid_tail_plan(K, large, cus).us; }
+
+hipError_t launch_gemm_mid_tail(BScale bmode, float amul, int64_t M, int64_t N, int64_t K, int cus, int first,
+                                const uint8_t* a, const uint8_t* a_scales, const float* a_dec, const uint8_t* b,
+                                const uint8_t* b_scales, const float* b_dec, void* c, bool c_bf16, hipStream_t s) {
+    const int64_t large = ((M + BM - 1) / BM) * ((N + BN - 1) / BN) - first;
+    const MidPlan p = mid_tail_plan(K, large, cus);
+    return bmode == BScale::Row
+               ? launch_mid_b<(int)BScale::Row>(p, first, M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16,
+                                                amul, s)
+               : launch_mid_b<(int)BScale::Tile>(p, first, M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16,
+                                                 amul, s);
 }
 
 }  // namespace ue5m3

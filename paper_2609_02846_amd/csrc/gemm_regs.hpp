@@ -13,6 +13,27 @@
 namespace ue5m3 {
 namespace {
 
+// The large output tile, and how tiles are dealt to the XCDs.
+constexpr int BM = 256, BN = 256;
+constexpr int kXcds = 8;
+constexpr int kGroupM = 4;
+
+// Origin of logical tile t: workgroups are dispatched round-robin over the
+// XCDs, so logical tiles are remapped to give each XCD a contiguous range,
+// walked in groups of kGroupM tile rows (column-major inside a group) so
+// that tiles running together on one XCD share A and B rows in its L2.
+__device__ __forceinline__ void tile_origin(int t, int tiles_m, int tiles_n, int64_t& m0, int64_t& n0) {
+    const int ntiles = tiles_m * tiles_n;
+    if (ntiles % kXcds == 0) t = (t % kXcds) * (ntiles / kXcds) + t / kXcds;
+    const int group_tiles = kGroupM * tiles_n;
+    const int g = t / group_tiles;
+    const int first_m = g * kGroupM;
+    const int gm = min(tiles_m - first_m, kGroupM);
+    const int rr = t - g * group_tiles;
+    m0 = (int64_t)(first_m + rr % gm) * BM;
+    n0 = (int64_t)(rr / gm) * BN;
+}
+
 // Instruction classes for the scheduling-group builtins.
 constexpr int kSgValu = 0x002, kSgMfma = 0x008, kSgVmemRead = 0x020, kSgDsRead = 0x100;
 

@@ -21,15 +21,15 @@ enum class ScaleKind : int { UE5M3 = 0, E4M3 = 1, E8M0 = 2 };
 // need and replaced by a larger one on demand (the replaced buffer is kept,
 // not freed, until the process ends): split-tile partials of the GEMMs,
 // block-32 scales expanded to the block-16 layout, per-workgroup partial
-// maxima of the amax kernels, scale codes in rows padded to 256 k.
-enum WorkspaceKind : int { kWsSplit = 0, kWsScales = 1, kWsAmax = 2, kWsPad = 3, kWsKinds = 4 };
+// maxima of the amax kernels.
+enum WorkspaceKind : int { kWsSplit = 0, kWsScales = 1, kWsAmax = 2, kWsKinds = 3 };
 
 // One call's use of a workspace.  Uses on one stream are ordered by the
 // stream as long as each call's launches are enqueued together, so the
 // workspace is held, against other host threads on the same stream, from
 // take() to the end of this object's life: keep it until the last launch
 // that touches the buffer is enqueued.  A call that needs several kinds takes
-// them in the order kWsScales, kWsSplit, kWsPad.  take() returns
+// them in the order kWsScales, kWsSplit.  take() returns
 // hipErrorStreamCaptureUnsupported when s is capturing and an allocation
 // would be needed.
 struct WorkspaceSlot;
@@ -119,11 +119,13 @@ hipError_t launch_gemm_mid(BScale bmode, float amul, int64_t M, int64_t N, int64
                            const uint8_t* a_scales, const float* a_dec, const uint8_t* b, const uint8_t* b_scales,
                            const float* b_dec, void* c, bool c_bf16, hipStream_t s);
 
-// Bytes of that array: 64 MiB for 256 partial tiles of 256 x 256 fp32, the
-// largest split
-// plan on a device of up to 256 compute units (the leftover tiles times their
-// parts never exceed the unit count), and 16 MiB for padded scale codes.
-constexpr size_t kNoallocBytes = (size_t)80 << 20;
+// The large (256 x 256) output tiles from index `first` on, in smaller ones:
+// the partial last wave of a product that cannot split it along K.
+// mid_tail_time: the modelled time in us of `large` of them.
+double mid_tail_time(int64_t K, int64_t large, int cus);
+hipError_t launch_gemm_mid_tail(BScale bmode, float amul, int64_t M, int64_t N, int64_t K, int cus, int first,
+                                const uint8_t* a, const uint8_t* a_scales, const float* a_dec, const uint8_t* b,
+                                const uint8_t* b_scales, const float* b_dec, void* c, bool c_bf16, hipStream_t s);
 
 // The allocation-free GEMM's scratch array on the current device: its
 // device address (taken once per device) and capacity in floats.

@@ -14,7 +14,10 @@
 namespace ue5m3 {
 namespace {
 
-constexpr size_t kScratchFloats = kNoallocBytes / sizeof(float);
+// 64 MiB: 256 partial tiles of 256 x 256 fp32, the largest split plan on a
+// device of up to 256 compute units (the leftover tiles times their parts
+// never exceed the unit count).
+constexpr size_t kScratchFloats = (size_t)1 << 24;
 
 static __device__ __align__(256) float scratch[kScratchFloats];
 

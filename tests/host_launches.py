@@ -66,3 +66,32 @@ def together(threads, reps, call):
     how many of them had another call's launch between their own)."""
     w = _run([f"together {threads} {reps} {call}"])[0].split()
     return int(w[0]), int(w[2]), int(w[4])
+
+
+def short(kernel):
+    """A kernel's short name: "large" (256 x 256 tiles; "masked": the
+    per-element epilogue, "ragged K": K % 256 != 0), "64x128 k2" (small tiles,
+    K groups), "stream 2x1 w8" (few rows: row groups, weight-row groups,
+    waves), "staged", "general", "sum" (split tiles), "codes" (blocks of 32),
+    "pm 128" (probe-matched tile), "mx"."""
+    name, _, rest = kernel.partition("<")
+    a = [w.strip() == "true" if w.strip() in ("true", "false") else int(w) for w in rest.rstrip(">").split(",") if w]
+    if name == "gemm_fp4_reg_kernel":
+        return "large" + ("" if a[2] else " masked") + (" ragged K" if a[3] else "")
+    if name == "gemm_fp4_mid_kernel":
+        return f"{64 * a[1]}x{64 * a[2]}" + (" k2" if a[3] == 2 else "")
+    if name == "gemm_fp4_skinny_kernel":
+        return f"stream {a[1]}x{a[2]} w{a[3]}"
+    if name == "gemm_pm_kernel":
+        return f"pm {64 * a[1]}"
+    if name == "gemm_mx_kernel":
+        return "mx" + ("" if a[1] else " masked")
+    return {"gemm_fp4_dma_kernel": "staged", "gemm_fp4_kernel": "general", "gemm_split_sum_kernel": "sum",
+            "copy_scales_kernel": "codes"}.get(name, name)
+
+
+def routes(calls):
+    """The short kernel names of each call, all of which must succeed."""
+    res = launches(calls)
+    assert all(status == 0 for status, _ in res), res
+    return [[short(k) for k, _, _ in kernels] for _, kernels in res]

@@ -1,8 +1,11 @@
 """Large decoded-operand products whose K is not a multiple of 256 (256 x 256
-tiles on padded scale codes): odd and even stage counts, K / 16 odd (the last
-row ends inside a 16-byte chunk), a split last wave, ragged M and N, both scale
-layouts, the allocation-free call, and a capture that can have no workspace.
-Raw codes; reference in float64 with the fp32 accumulation bound."""
+tiles whose last stage runs past the rows' end): odd and even stage counts,
+K / 16 odd (the last row ends inside a 16-byte chunk), leftover tiles in every
+smaller size, ragged M and N, both epilogues and scale layouts, the
+allocation-free call, and a capture on a stream without workspaces, which
+has to run the same kernels.  Raw codes; reference in float64 with the fp32
+accumulation bound.  The kernels named per case are checked on the host
+(test_host_launches.py)."""
 
 import pytest
 import torch
@@ -25,8 +28,21 @@ def _operand(rows, K, tiled, seed):
     return p, s, torch.cat([mag, -mag])[nib] * (sv.repeat_interleave(16, 0) if tiled else sv)
 
 
-@pytest.mark.parametrize("layout,M,N,K", [("nt", 4096, 4096, 4080), ("tn", 4222, 4397, 2064), ("nn", 4100, 4400, 2064),
-                                          ("tn", 4097, 4096, 4048)])
+# (layout, M, N, K), kernels
+CASES = [
+    (("nt", 4096, 4096, 4080), ["large ragged K"]),                                # 16 stages
+    (("tn", 4096, 4096, 2064), ["large ragged K"]),                                # 9 stages
+    (("tn", 4089, 4094, 2064), ["large masked ragged K"]),
+    (("tn", 4097, 4096, 4048), ["large ragged K", "64x64 k2"]),                    # 16 tiles left over
+    (("nn", 4090, 4592, 4080), ["large ragged K", "64x128 k2"]),                   # 32
+    (("tn", 4222, 4397, 2064), ["large masked ragged K", "128x128 k2"]),           # 50
+    (("nn", 4100, 4400, 2064), ["large ragged K", "128x128 k2"]),                  # 50
+    (("tn", 4093, 6141, 4048), ["large masked ragged K", "128x128"]),              # 128
+    (("tn", 8190, 4099, 2064), ["large masked ragged K", "64x128 k2"]),            # two whole waves and 32
+]
+
+
+@pytest.mark.parametrize("layout,M,N,K", [c for c, _ in CASES])
 def test_padded_scale_codes(layout, M, N, K):
     say("padded gemm", layout, M, N, K)
     a, sa, A = _operand(M, K, False, 51)
@@ -45,7 +61,7 @@ def test_padded_scale_codes(layout, M, N, K):
     ue.gemm_noalloc(*args, na)
     torch.cuda.synchronize()
     assert torch.equal(na, c)
-    # a capturing stream without workspaces: another kernel runs, no refusal
+    # a capturing stream without workspaces: the same kernels and bits
     out = torch.zeros(M, N, device="cuda")
     st, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
     torch.cuda.synchronize()
@@ -55,4 +71,4 @@ def test_padded_scale_codes(layout, M, N, K):
         out.zero_()
         g.replay()
         torch.cuda.synchronize()
-        assert ok(out)
+        assert torch.equal(out, c)

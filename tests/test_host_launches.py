@@ -3,7 +3,8 @@ what order (see host_launches.py)."""
 
 import pytest
 
-from tests.host_launches import amax_call, gemm_call, launches, together
+from tests import test_gpu_gemm_padded as padded
+from tests.host_launches import amax_call, gemm_call, launches, routes, together
 
 # Calls of several launches that pass data through a library workspace:
 # (what, call, launches)
@@ -13,7 +14,6 @@ CHAINS = [
     ("codes of blocks of 32", gemm_call("nt", 2048, 2048, 1024, block=32), 2),
     ("codes of blocks of 32, then split tiles", gemm_call("nt", 4096, 4352, 1024, block=32), 3),
     ("codes of blocks of 32, probe-matched", gemm_call("nt", 512, 512, 512, block=32, entry="pm"), 2),
-    ("scale codes padded for K, then split tiles", gemm_call("tn", 6144, 4096, 2000), 3),
     ("partial maxima", amax_call(1 << 20), 2),
 ]
 
@@ -37,3 +37,14 @@ def test_few_rows_of_very_many_columns_launch(M, N):
     assert status == 0
     assert [k.split("<")[0] for k, _, _ in kernels] == ["gemm_fp4_skinny_kernel" if N <= (1 << 29) - 32
                                                         else "gemm_fp4_kernel"]
+
+
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+def test_products_of_ragged_k_take_no_workspace(out):
+    """A product whose K is not a multiple of 256 runs the same kernels on a
+    capturing stream that has no workspace, in an eager call and in the
+    allocation-free one, so that their results are equal."""
+    for case, kernels in padded.CASES:
+        calls = [gemm_call(*case, out=out, stream=1, capturing=True), gemm_call(*case, out=out, stream=2),
+                 gemm_call(*case, out=out, entry="noalloc")]
+        assert routes(calls) == [kernels] * 3, case
