@@ -1179,6 +1179,19 @@ __device__ __forceinline__ void mfma_mx(f32x16_t& acc, const uint32_t (&a)[4], c
                      : "+a"(acc) : "v"(av), "v"(bv), "v"(sa), "v"(sb));
 }
 
+// A slice's scale words shifted by the lane half's byte, eight of them.  One
+// instruction sequence that stays behind the products before it.
+__device__ __forceinline__ void mx_shift8(uint32_t (&o)[4][2], const uint2* in, uint32_t sh) {
+    asm volatile(
+        "v_lshrrev_b32 %0, %16, %8\n\tv_lshrrev_b32 %1, %16, %9\n\tv_lshrrev_b32 %2, %16, %10\n\t"
+        "v_lshrrev_b32 %3, %16, %11\n\tv_lshrrev_b32 %4, %16, %12\n\tv_lshrrev_b32 %5, %16, %13\n\t"
+        "v_lshrrev_b32 %6, %16, %14\n\tv_lshrrev_b32 %7, %16, %15"
+        : "=&v"(o[0][0]), "=&v"(o[0][1]), "=&v"(o[1][0]), "=&v"(o[1][1]), "=&v"(o[2][0]), "=&v"(o[2][1]),
+          "=&v"(o[3][0]), "=&v"(o[3][1])
+        : "v"(in[0].x), "v"(in[0].y), "v"(in[1].x), "v"(in[1].y), "v"(in[2].x), "v"(in[2].y), "v"(in[3].x),
+          "v"(in[3].y), "v"(sh));
+}
+
 // The wave's loads and LDS accesses done, then the workgroup barrier.
 __device__ __forceinline__ void wait_all_barrier() {
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -1293,8 +1306,19 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_mx_kernel(
 
     f32x16_t acc[4][4];
     MxSlice R0, R1;
-    uint32_t sc[8][2];
-    uint2 scn[8];
+    uint32_t sa[4][2], sb[4][2];                     // scales of the A and B rows of the stage
+    uint2 scn[8];                                    // raw words of the next stage
+    // Slice SL takes bytes 2 SL + l/32 of each row's 8 codes: dword SL / 2
+    // shifted by the lane half, byte 0 or 2.  The shifts of the next stage
+    // follow a stage's last product and, with the wait states after them, are
+    // what lets that product land (21 states; one of 16 passes needs 20)
+    // before anything the compiler may place where the stage loop closes.
+    auto shift_scales = [&]() {
+        mx_shift8(sa, scn, 8u * hi);
+        mx_shift8(sb, scn + 4, 8u * hi);
+        asm volatile("s_nop 4" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
 
     // stage 0 complete everywhere, stage 1 in flight
     load_scales();
@@ -1310,8 +1334,9 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_mx_kernel(
     }
     advance();
     static_for<0, kSupPayLoads>([&](auto ic) { load(ic, 1); });
+    shift_scales();
 
-    int b = 0, sb = 0;                               // payload and scale buffers of the current stage
+    int b = 0, sbuf = 0;                             // payload and scale buffers of the current stage
     for (int k = 0; k < nw; ++k) {
         const WorkItem cur = work_item(item_at(k), sp, NG);
         const int next_g0 = work_item(item_at(min(k + 1, nw - 1)), sp, NG).g0;
@@ -1325,20 +1350,13 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_mx_kernel(
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j) asm volatile("" : "+a"(acc[i][j]));
+        // the products are instructions the compiler does not model: keep the
+        // zeros clear of them
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_nop 4" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
 
         for (int st = cur.g0; st < cur.g1; ++st) {
-            // slice SL takes bytes 2 SL + l/32 of each row's 8 codes: dword SL / 2
-            // shifted by the lane half, byte 0 or 2
-#pragma unroll
-            for (int g = 0; g < 8; ++g) {
-                sc[g][0] = scn[g].x >> (8 * hi);
-                sc[g][1] = scn[g].y >> (8 * hi);
-            }
-            // the products are instructions the compiler does not model: keep
-            // the accumulator and scale writes clear of them
-            __builtin_amdgcn_sched_barrier(0);
-            asm volatile("s_nop 4" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
             // 16 products on Rc (issued as B x A^T, see store_item) with the
             // reads of the next slice and, in slice 3, the loads of the stage
             // after the next spread between them.  (Half of those loads in
@@ -1347,13 +1365,13 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_mx_kernel(
             const int bn = b ^ 1;
             const bool last = st + 1 == cur.g1;
             const int gn = last ? next_g0 : st + 1;              // the next stage and its scale buffer
-            const int sbn = last || (gn & 1) == 0 ? sb ^ 1 : sb;
+            const int sbn = last || (gn & 1) == 0 ? sbuf ^ 1 : sbuf;
             const int at = sbn * kMxScl + (gn & 1) * 8;
             auto slice = [&](auto SLc, MxSlice& Rc, MxSlice& Rn, int rbuf, int xo) {
                 constexpr int SL = decltype(SLc)::value;
                 static_for<0, 16>([&](auto qc) {
                     constexpr int q = decltype(qc)::value, i = q / 4, j = q % 4;
-                    mfma_mx<2 * (SL % 2)>(acc[i][j], Rc.w[4 + j], Rc.w[i], sc[4 + j][SL / 2], sc[i][SL / 2]);
+                    mfma_mx<2 * (SL % 2)>(acc[i][j], Rc.w[4 + j], Rc.w[i], sb[j][SL / 2], sa[i][SL / 2]);
                     if constexpr (q % 2 == 0) {
                         read_group(Rn, q / 2, rbuf, xo);
                         if constexpr (SL == 3) read_scale(scn[q / 2], q / 2, at);
@@ -1373,8 +1391,9 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_mx_kernel(
             wait_all_barrier();
             advance();
             slice(I3{}, R1, R0, bn, x0);
+            shift_scales();
             b = bn;
-            sb = sbn;
+            sbuf = sbn;
         }
         // give the last products time to land before their results are read
         asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
