@@ -23,8 +23,8 @@
 //    per workgroup into a double-buffered fp16 LDS stage, and
 //    gemm_fp4_kernel for any K % 16 == 0, the same with register-staged
 //    loads (it also writes the zeros of K = 0).
-// Few output rows run in gemm_skinny.hip, calls that fill the chip better in
-// smaller tiles in gemm_mid.hip (launch_mode).
+// Few output rows run in gemm_skinny.hip (launch_gemm), calls that fill the
+// chip better in smaller tiles in gemm_mid.hip (launch_mode).
 // Decoding writes each UE5M3 scale s as mu * 2^E (mu = 1 + m/8 in [1, 2), or
 // 0 for code 0) or reads the code as an fp16 bit pattern (c << 7 is its
 // value).  The gfx950 FP4 -> FP16 conversion applies a power-of-two scale
@@ -1672,7 +1672,7 @@ double reg_time(int64_t M, int64_t N, int64_t K, int cus) {
 }
 
 template <int BMODE>
-hipError_t launch_mode(int64_t M, int64_t N, int64_t K, const uint8_t* a, const uint8_t* as,
+hipError_t launch_mode(int cus, int64_t M, int64_t N, int64_t K, const uint8_t* a, const uint8_t* as,
                        const float* ad, const uint8_t* b, const uint8_t* bs, const float* bd,
                        void* c, bool c_bf16, float amul, hipStream_t s, const FixedScratch* fx) {
     // the register-decode kernels address operands (and, in 256 x 256 tiles,
@@ -1682,9 +1682,6 @@ hipError_t launch_mode(int64_t M, int64_t N, int64_t K, const uint8_t* a, const 
     const bool reg = K >= 256 && M * (Kp / 2) < kLim && N * (Kp / 2) < kLim && M * N * 4 < kLim;
     const bool mid = mid_gemm_fits(M, N, K);
     if (reg || mid) {
-        int cus = 0;
-        hipError_t e = device_cus(&cus);
-        if (e != hipSuccess) return e;
         if (mid && (!reg || mid_gemm_time(M, N, K, cus) < reg_time(M, N, K, cus)))
             return launch_gemm_mid((BScale)BMODE, amul, M, N, K, cus, a, as, ad, b, bs, bd, c, c_bf16, s);
         const RegPlan p = reg_plan(M, N, K, cus);
@@ -1700,7 +1697,7 @@ hipError_t launch_mode(int64_t M, int64_t N, int64_t K, const uint8_t* a, const 
             if (p.floats > fx->floats) return hipErrorOutOfMemory;
             part = fx->part;
         } else if (p.floats > 0) {
-            e = split_workspace(held, s, p.floats, &part);
+            const hipError_t e = split_workspace(held, s, p.floats, &part);
             if (e != hipSuccess) return e;
         }
         return c_bf16 ? launch_reg<BMODE, true, false>(p, cus, part, M, N, K, a, as, ad, b, bs, bd, c, amul, s)
@@ -1720,17 +1717,24 @@ hipError_t launch_gemm(BScale bmode, float amul, int64_t M, int64_t N, int64_t K
                        const uint8_t* b_scales, const float* b_dec, void* c, bool c_bf16,
                        hipStream_t s, const FixedScratch* fx) {
     if (M == 0 || N == 0) return hipSuccess;
-    if (skinny_gemm(M, N, K))
+    int cus = 0;
+    bool few = M <= 32 && skinny_gemm(M, N, K, cus);     // a choice that needs no device query
+    if (!few) {
+        const hipError_t e = device_cus(&cus);
+        if (e != hipSuccess) return e;
+        few = skinny_gemm(M, N, K, cus);
+    }
+    if (few)
         return launch_gemm_skinny(bmode, amul, M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16, s);
     switch (bmode) {
         case BScale::Row:
-            return launch_mode<(int)BScale::Row>(M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16, amul, s,
+            return launch_mode<(int)BScale::Row>(cus, M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16, amul, s,
                                                  fx);
         case BScale::Tile:
-            return launch_mode<(int)BScale::Tile>(M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16, amul,
+            return launch_mode<(int)BScale::Tile>(cus, M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16, amul,
                                                   s, fx);
         case BScale::TileDgrad:
-            return launch_mode<(int)BScale::TileDgrad>(M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16,
+            return launch_mode<(int)BScale::TileDgrad>(cus, M, N, K, a, a_scales, a_dec, b, b_scales, b_dec, c, c_bf16,
                                                        amul, s, fx);
     }
     return hipErrorInvalidValue;

@@ -3,7 +3,8 @@
 // Same operands, decode and result contract as the kernels of gemm.hip; any
 // K % 16 == 0, any size of operand (64-bit addresses) with N < 2^29.
 //
-// Bound: reading B, the quantized weight, once (N K / 2 bytes).  A 256 x 256
+// Bound: reading B, the quantized weight, once (N K / 2 bytes); with more than
+// 32 rows the decode of A (skinny_gemm).  A 256 x 256
 // output tile gives a weight of N rows only N / 256 workgroups that each walk
 // all of K; here a workgroup owns 16 (NT = 1) or 32 (NT = 2) weight rows and
 // its waves split K among themselves, so that every CU streams its share of
@@ -11,8 +12,8 @@
 // (added in wave order: the result does not depend on timing, and no
 // workspace is needed).  Measured against the 256 x 256 tiles: 1 x 6144 x
 // 4096 72.5 -> 5.9 us, 1 x 21504 x 4096 72.8 -> 10.9 us (4.1 TB/s of
-// payload), 24 x 21504 x 4096 72.6 -> 17.7 us, 64 x 21504 x 4096 73.0 ->
-// 30.5 us, 32 x 4096 x 21504 349 -> 27 us.
+// payload), 24 x 21504 x 4096 72.6 -> 17.7 us, 64 x 6144 x 4096 72.6 ->
+// 12.8 us, 32 x 4096 x 21504 349 -> 27 us.
 //
 // v_mfma_f32_16x16x32_f16 with the weight as the row operand: lane l supplies
 // 8 k-elements of weight row l % 16 and of A row l % 16, k group l / 16.  A
@@ -240,9 +241,22 @@ hipError_t launch_skinny_b(int64_t M, int64_t N, int64_t K, const uint8_t* a, co
 
 }  // namespace
 
-bool skinny_gemm(int64_t M, int64_t N, int64_t K) {
+bool skinny_gemm(int64_t M, int64_t N, int64_t K, int cus) {
     // a launch dimension holds less than 2^32 work-items: N / 32 workgroups of 256
-    return M > 0 && M <= 64 && K > 0 && N > 0 && N <= ((int64_t)1 << 29) - 32;
+    if (M <= 0 || M > 64 || K <= 0 || N <= 0 || N > ((int64_t)1 << 29) - 32) return false;
+    // Up to 32 rows the weight's bytes bound the call.  Above, the decode of A,
+    // which every workgroup repeats, does: the small tiles are ahead once the
+    // workgroups of 32 weight rows outnumber the CUs, and where K is so short
+    // that a wave's four steps in flight (2048 k of the workgroup) reach past
+    // it.  Measured on 256 CUs, here / small tiles, us: 64 x 21504 x 4096 30.5
+    // / 22, 33 x 21504 x 8192 45.5 / 39.8, 64 x 12288 x 8192 39.9 / 28.4, 33 x
+    // 12288 x 2048 9.9 / 9.7, 64 x 65536 x 4096 89 / 46; 64 x 8192 x 4096 13.0
+    // / 15.7, 64 x 8192 x 2048 8.3 / 9.6, 33 x 2048 x 4096 11.5 / 15.1; 64 x
+    // 1024 x 512 5.9 / 4.5, 33 x 256 x 1024 6.5 / 6.2, 64 x 4096 x 1024 7.7 /
+    // 6.3, 64 x 1024 x 1536 7.7 / 8.0.  At 17 to 32 rows the two cross over only
+    // far out (32 x 21504 x 4096 19.5 / 22, 17 x 32768 x 4096 20.5 / 22.8, 24 x
+    // 32768 x 4096 23.5 / 22.8, 32 x 65536 x 4096 54.7 / 42.9).
+    return M <= 32 || (N <= 32 * (int64_t)cus && K > 1024) || !mid_gemm_fits(M, N, K);
 }
 
 hipError_t launch_gemm_skinny(BScale bmode, float amul, int64_t M, int64_t N, int64_t K, const uint8_t* a,

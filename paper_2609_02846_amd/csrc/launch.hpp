@@ -103,9 +103,10 @@ hipError_t launch_gemm(BScale bmode, float amul, int64_t M, int64_t N, int64_t K
                        const uint8_t* b, const uint8_t* b_scales, const float* b_dec,
                        void* c, bool c_bf16, hipStream_t s, const FixedScratch* fx = nullptr);
 
-// The same GEMM for few output rows (M <= 64), where reading B bounds the
-// call: no workspace, any K % 16 == 0.
-bool skinny_gemm(int64_t M, int64_t N, int64_t K);
+// The same GEMM for few output rows (M <= 64): no workspace, any K % 16 == 0.
+// skinny_gemm: whether it serves the call best on a device of `cus` compute
+// units.
+bool skinny_gemm(int64_t M, int64_t N, int64_t K, int cus);
 hipError_t launch_gemm_skinny(BScale bmode, float amul, int64_t M, int64_t N, int64_t K, const uint8_t* a,
                               const uint8_t* a_scales, const float* a_dec, const uint8_t* b,
                               const uint8_t* b_scales, const float* b_dec, void* c, bool c_bf16, hipStream_t s);

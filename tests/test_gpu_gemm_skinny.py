@@ -1,7 +1,9 @@
-"""Decoded-operand GEMM with few output rows (M <= 64, the streaming kernel):
+"""Decoded-operand GEMM with few output rows (M <= 64): the streaming kernel at
 every group count, both weight-row widths, short and long K, K with a partial
-step, the last M and N, both output types and both scale layouts, against the
-oracle to the GEMM bar."""
+step, the last M and N, and both sides of the lines beyond which more than 32
+rows run in small tiles; both output types and scale layouts, against the
+oracle to the GEMM bar.  The kernels named per case are checked on the host
+(test_host_launches.py)."""
 
 import pytest
 import torch
@@ -15,13 +17,21 @@ from tests.gpu_util import f32_scalar_dev, gemm_check, host, say, u8_to_dev
 
 pytestmark = pytest.mark.gpu
 
-# (layout, M, N, K): N below and above both width limits, K % 128 != 0, K past
-# the wave-count limit, single rows and the last row count of each group
-CASES = [("nt", 1, 256, 128), ("nt", 16, 4096, 16), ("nt", 17, 48, 4112), ("tn", 33, 4103, 144),
-         ("nn", 32, 8192, 272), ("tn", 64, 8195, 256), ("nt", 64, 4096, 1040), ("tn", 5, 37, 4224)]
+# (layout, M, N, K), kernel: N below and above both width limits, K % 128 != 0,
+# K past the wave-count limit, single rows and the last row count of each group
+CASES = [
+    (("nt", 1, 256, 128), "stream 1x1 w4"), (("nt", 16, 4096, 16), "stream 1x1 w4"),
+    (("tn", 5, 37, 4224), "stream 1x1 w8"), (("tn", 16, 8195, 144), "stream 1x2 w4"),
+    (("nt", 17, 48, 4112), "stream 2x1 w8"), (("nt", 32, 1040, 4096), "stream 2x1 w4"),
+    (("nn", 32, 8192, 272), "stream 2x2 w4"), (("tn", 29, 8209, 2048), "stream 2x2 w4"),
+    (("nt", 64, 2048, 1040), "stream 4x1 w4"), (("tn", 33, 4095, 4240), "stream 4x1 w8"),
+    (("nt", 64, 4096, 1040), "stream 4x2 w4"), (("nn", 33, 8192, 1152), "stream 4x2 w4"),
+    (("tn", 33, 4103, 144), "64x64"), (("tn", 64, 8195, 256), "64x64"), (("nt", 64, 4096, 1024), "64x64"),
+    (("tn", 64, 8193, 1040), "64x64"), (("nt", 33, 21504, 2064), "64x128 k2"),
+]
 
 
-@pytest.mark.parametrize("layout,M,N,K", CASES)
+@pytest.mark.parametrize("layout,M,N,K", [c for c, _ in CASES])
 def test_few_rows(layout, M, N, K):
     say("skinny gemm", layout, M, N, K)
     tiled = layout != "tn"

@@ -4,6 +4,7 @@ what order (see host_launches.py)."""
 import pytest
 
 from tests import test_gpu_gemm_padded as padded
+from tests import test_gpu_gemm_skinny as few_rows
 from tests.host_launches import amax_call, gemm_call, launches, routes, together
 
 # Calls of several launches that pass data through a library workspace:
@@ -48,3 +49,21 @@ def test_products_of_ragged_k_take_no_workspace(out):
         calls = [gemm_call(*case, out=out, stream=1, capturing=True), gemm_call(*case, out=out, stream=2),
                  gemm_call(*case, out=out, entry="noalloc")]
         assert routes(calls) == [kernels] * 3, case
+
+
+@pytest.mark.parametrize("entry", ["gemm", "noalloc"])
+def test_few_rows_run_where_the_gpu_tests_say(entry):
+    assert routes([gemm_call(*c, entry=entry) for c, _ in few_rows.CASES]) == [[k] for _, k in few_rows.CASES]
+
+
+def test_few_rows_leave_the_streaming_kernel_only_above_32():
+    """More than 32 rows: small tiles once the workgroups of 32 weight rows
+    outnumber the 256 CUs or K is at most 1024, unless the weight is too large
+    for them (2^31 bytes)."""
+    stream = lambda M, N, K: routes([gemm_call("nt", M, N, K)])[0][0].startswith("stream")  # noqa: E731
+    for M in (1, 16, 17, 32):
+        assert all(stream(M, N, K) for N in (16, 8192, 8208, 65536) for K in (16, 1024, 1040, 8192))
+    for M in (33, 64):
+        assert all(stream(M, N, K) == (N <= 8192 and K > 1024) for N in (16, 8192, 8208, 65536)
+                   for K in (16, 1024, 1040, 8192))
+        assert stream(M, 131072, 32768)
