@@ -68,7 +68,8 @@ def test_three_products(T, K, N):
 
 
 def test_ragged_m_and_n():
-    """M not a multiple of the tile (fprop rows), N ragged for wgrad."""
+    """M not a multiple of the tile (fprop rows), N ragged for wgrad, in the
+    kernels that small sizes run on (streaming and small tiles)."""
     say("gemm ragged")
     for M, N, K in [(37, 48, 80), (130, 144, 48), (1, 16, 16), (200, 16, 1024)]:
         a = synthetic.activation(3, M, K, 1e-2, 50.0)
@@ -297,10 +298,10 @@ def test_single_small_linear_fprop():
 
 @pytest.mark.parametrize("out", ["bf16", "f32"])
 def test_vector_epilogue_edges(out):
-    """The staged whole-tile epilogue (bf16 with N % 8 == 0, fp32 with
-    N % 4 == 0): output rows past M inside a 32-row round, 8-column (4-column)
-    runs past N inside a 64-column (32-column) round, and more than one tile
-    in each direction."""
+    """The vector stores of the streaming kernel and the small tiles (bf16 with
+    N % 8 == 0, fp32 with N % 4 == 0): output rows past M inside a 32-row round,
+    8-column (4-column) runs past N, and more than one tile in each direction.
+    test_gpu_gemm_kernels.py has the 256 x 256 tiles' epilogues."""
     say("gemm vector epilogue edges", out)
     Ns = [8, 24, 40, 136, 264] if out == "bf16" else [4, 12, 36, 132, 260]
     for M, N, K in [(1, Ns[0], 64), (37, Ns[1], 128), (259, Ns[2], 256), (300, Ns[3], 512), (517, Ns[4], 256)]:
@@ -326,9 +327,8 @@ def test_vector_epilogue_edges(out):
 
 def test_bf16_small_m_wide_n():
     """bf16 output with few rows and very many columns (16 x 12582912, K =
-    256: the register-decode kernel): the padded tile rows' byte offsets pass
-    2^32 there, so the vector epilogue (which drops rows past M by their
-    offset) must not be used.  B repeats a block of 768 random rows, so every
+    256, in the streaming kernel): a padded 256-row tile's byte offsets would
+    pass 2^32 there.  B repeats a block of 768 random rows, so every
     output column equals one of 768 columns the oracle computes, and all
     201 million outputs are compared with it."""
     M, N, K, P = 16, 3 << 22, 256, 768
@@ -366,13 +366,13 @@ def _random_operands(g, M, N, K, block, codes):
 
 
 @pytest.mark.parametrize("entry,M,N,K,dt,fmt,block", [
-    ("gemm", 300, 136, 512, "bf16", "ue5m3", 16),      # vector epilogue, bf16
-    ("gemm", 300, 132, 512, "f32", "ue5m3", 16),       # vector epilogue, fp32
-    ("gemm", 37, 140, 512, "bf16", "ue5m3", 16),       # per-element epilogue (N % 8 = 4)
-    ("gemm", 37, 130, 512, "f32", "ue5m3", 16),        # per-element epilogue (N % 4 = 2)
+    ("gemm", 300, 136, 512, "bf16", "ue5m3", 16),      # small tiles, vector stores, bf16
+    ("gemm", 300, 132, 512, "f32", "ue5m3", 16),       # small tiles, vector stores, fp32
+    ("gemm", 37, 140, 512, "bf16", "ue5m3", 16),       # per-element stores (N % 8 = 4)
+    ("gemm", 37, 130, 512, "f32", "ue5m3", 16),        # per-element stores (N % 4 = 2)
     ("gemm", 4252, 4096, 1024, "bf16", "ue5m3", 16),   # split leftover tiles, ragged M
-    ("gemm", 300, 136, 192, "bf16", "ue5m3", 16),      # K % 256 != 0: staged kernel
-    ("gemm", 37, 40, 48, "f32", "ue5m3", 16),          # K % 64 != 0: general kernel
+    ("gemm", 300, 136, 192, "bf16", "ue5m3", 16),      # K % 256 != 0
+    ("gemm", 37, 40, 48, "f32", "ue5m3", 16),          # K % 64 != 0
     ("gemm", 300, 136, 512, "bf16", "ue5m3", 32),      # blocks of 32
     ("gemm", 300, 136, 512, "bf16", "e8m0", 32),       # E8M0 scales
     ("gemm_pm", 300, 136, 512, "bf16", "ue5m3", 16),   # probe-matched
@@ -386,8 +386,9 @@ def test_writes_exactly_c(entry, M, N, K, dt, fmt, block):
     C has: the guard after C spans the rows of the padded 256-row tile grid
     past M and one more tile row, which holds every store a tile of C could
     address.  Covers ragged M inside a tile and inside an epilogue round, the
-    vector and per-element epilogues, split leftover tiles, the staged and
-    general kernels, blocks of 32, E8M0 scales and the probe-matched GEMM."""
+    vector and per-element stores of the small tiles, split leftover tiles,
+    blocks of 32, E8M0 scales and the probe-matched GEMM;
+    test_gpu_gemm_kernels.py does the same on the other kernels."""
     say("gemm writes exactly C", entry, M, N, K, dt, fmt, block)
     dt = torch.bfloat16 if dt == "bf16" else torch.float32
     g = torch.Generator(device="cuda").manual_seed(M * 7 + N)

@@ -5,10 +5,11 @@ codes.  Here the payload bytes are uniform (all 16 nibbles, -0 included) and
 the block-scale codes run over every finite code of the format -- UE5M3
 0x00..0xF7 (subnormals m 2^-17, the 0x08 boundary 2^-14, up to 61440; Sec. 3
 and Table tab:scale-range) and E4M3 0x00..0x7E -- each code appearing many
-times in both operands.  The products run through all three decode kernels
-(K % 256 == 0: the persistent register-decode kernel; K % 64 == 0: the
-staged kernel; K % 16 == 0: the general kernel) for the three layouts'
-B-scale forms (tile scales for fprop and dgrad, row scales for wgrad).  The
+times in both operands.  At these sizes the products run in small tiles (64 x
+64), at three kinds of K (whole stages, whole slices, a partial slice) for the
+three layouts' B-scale forms (tile scales for fprop and dgrad, row scales for
+wgrad); test_gpu_gemm_kernels.py has every code on the other kernels, and
+test_gpu_large.py on those of operands past 2^31 bytes.  The
 operands are contraction-contiguous in every layout, so the reference is
 alpha * A_hat B_hat^T of the oracle's decoded operands, checked to the GEMM
 bar of tests/gpu_util.gemm_check."""

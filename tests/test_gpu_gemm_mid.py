@@ -1,7 +1,9 @@
 """Decoded-operand GEMM in 64- and 128-row tiles: every tile and K-group
 configuration at sizes whose last tile, last stage, last slice and last pair
 of blocks are partial (K / 16 odd: the last row ends inside a 16-byte chunk),
-both scale layouts and output types, against the oracle to the GEMM bar."""
+both scale layouts and output types, against the oracle to the GEMM bar.  The
+configurations named per case are checked on the host
+(test_host_launches.py)."""
 
 import pytest
 import torch
@@ -15,16 +17,20 @@ from tests.gpu_util import f32_scalar_dev, gemm_check, host, say, u8_to_dev
 
 pytestmark = pytest.mark.gpu
 
-CASES = [("nt", 71, 272, 16), ("tn", 129, 353, 80),            # 64 x 64 tiles
-         ("nt", 68, 352, 1680), ("tn", 68, 353, 1680),         # two K groups
-         ("nt", 71, 9392, 16), ("nn", 71, 9392, 272),          # 64 x 128
-         ("nt", 75, 9504, 1264), ("tn", 75, 9506, 1264),       # two K groups
-         ("nt", 73, 17888, 48), ("tn", 129, 17889, 528),       # 128 x 128
-         ("nt", 66, 17360, 2512), ("tn", 66, 17366, 2512),     # two K groups
-         ("nt", 300, 512, 512), ("nn", 200, 1024, 768)]        # K % 256 == 0
+# (layout, M, N, K), tile and K groups
+CASES = [
+    (("nt", 71, 272, 16), "64x64"), (("tn", 129, 353, 80), "64x64"),
+    (("nt", 68, 352, 1680), "64x64 k2"), (("tn", 68, 353, 1680), "64x64 k2"),
+    (("nt", 71, 9392, 16), "64x128"), (("nn", 71, 9392, 272), "64x128"), (("tn", 129, 17889, 528), "64x128"),
+    (("nt", 75, 9504, 1264), "64x128 k2"), (("tn", 75, 9506, 1264), "64x128 k2"),
+    (("nt", 73, 17888, 48), "128x128"), (("tn", 1100, 4103, 272), "128x128"), (("nn", 1030, 4112, 144), "128x128"),
+    (("nt", 777, 4096, 1040), "128x128"), (("tn", 777, 4099, 1040), "128x128"),
+    (("nt", 66, 17360, 2512), "128x128 k2"), (("tn", 66, 17366, 2512), "128x128 k2"),
+    (("nt", 300, 512, 512), "64x64"), (("nn", 200, 1024, 768), "64x64"),      # K % 256 == 0
+]
 
 
-@pytest.mark.parametrize("layout,M,N,K", CASES)
+@pytest.mark.parametrize("layout,M,N,K", [c for c, _ in CASES])
 def test_small_tiles(layout, M, N, K):
     say("mid gemm", layout, M, N, K)
     x = synthetic.activation(21, M, K, 0.01, 50.0)

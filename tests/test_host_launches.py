@@ -3,8 +3,11 @@ what order (see host_launches.py)."""
 
 import pytest
 
+from tests import test_gpu_gemm_kernels as kernels
+from tests import test_gpu_gemm_mid as small_tiles
 from tests import test_gpu_gemm_padded as padded
 from tests import test_gpu_gemm_skinny as few_rows
+from tests import test_gpu_large as large
 from tests.host_launches import amax_call, gemm_call, launches, routes, together
 
 # Calls of several launches that pass data through a library workspace:
@@ -45,15 +48,10 @@ def test_products_of_ragged_k_take_no_workspace(out):
     """A product whose K is not a multiple of 256 runs the same kernels on a
     capturing stream that has no workspace, in an eager call and in the
     allocation-free one, so that their results are equal."""
-    for case, kernels in padded.CASES:
+    for case, names in padded.CASES:
         calls = [gemm_call(*case, out=out, stream=1, capturing=True), gemm_call(*case, out=out, stream=2),
                  gemm_call(*case, out=out, entry="noalloc")]
-        assert routes(calls) == [kernels] * 3, case
-
-
-@pytest.mark.parametrize("entry", ["gemm", "noalloc"])
-def test_few_rows_run_where_the_gpu_tests_say(entry):
-    assert routes([gemm_call(*c, entry=entry) for c, _ in few_rows.CASES]) == [[k] for _, k in few_rows.CASES]
+        assert routes(calls) == [names] * 3, case
 
 
 def test_few_rows_leave_the_streaming_kernel_only_above_32():
@@ -67,3 +65,23 @@ def test_few_rows_leave_the_streaming_kernel_only_above_32():
         assert all(stream(M, N, K) == (N <= 8192 and K > 1024) for N in (16, 8192, 8208, 65536)
                    for K in (16, 1024, 1040, 8192))
         assert stream(M, 131072, 32768)
+
+
+def test_gemms_run_on_the_kernels_the_gpu_tests_name():
+    """The choice of kernel rests on fitted times: a test that is about one
+    kernel has to be at sizes that run on it (256 CUs)."""
+    for module in (few_rows, small_tiles):
+        for entry in ("gemm", "noalloc"):
+            assert routes([gemm_call(*c, entry=entry) for c, _ in module.CASES]) == [[k] for _, k in module.CASES]
+    for case, names in kernels.CASES:
+        fmt, block = case[4:]
+        calls = [gemm_call(*case[:4], out=out, fmt=fmt, block=block) for out in ("f32", "bf16")]
+        if fmt == "ue5m3" and block == 16:
+            calls.append(gemm_call(*case[:4], entry="noalloc"))
+        assert routes(calls) == [names] * len(calls), case
+    for case, names in kernels.SMALLEST:
+        assert routes([gemm_call(*case), gemm_call(*case, fmt="e4m3")]) == [names] * 2, case
+    for case, name in large.OPERAND_CASES:
+        assert routes([gemm_call(*case)]) == [[name]], case
+    for case, name in large.OUTPUT_CASES:
+        assert routes([gemm_call(*case), gemm_call(*case, out="bf16")]) == [[name]] * 2, case
