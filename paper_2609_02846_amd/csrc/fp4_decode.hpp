@@ -55,57 +55,30 @@ struct RowSlice {
     uint32_t code[4];     // scale code of each block (low byte)
 };
 
-// Per-thread operand row: payload row pointer and scale addressing.
+// Per-thread operand row.
 struct RowSrc {
     const uint8_t* pay;   // payload row (K/2 bytes)
-    const uint8_t* sc;    // scale of block 0 of this row
-    int64_t sc_stride;    // byte distance between consecutive k-blocks' scales
+    const uint8_t* sc;    // its scale codes
 };
 
-// FULLK: K % 64 == 0, so every slice has 4 whole blocks, payload rows are
-// 16-byte aligned and (for row/tile scales) 4 scale codes are one aligned
-// word.  Otherwise blocks at or past K are clamped on load and zeroed at
+// Blocks at or past K (kbt of them in a row) are clamped on load and zeroed at
 // decode.  Rows past M or N are clamped to the last row: their results fall
 // in output rows/columns that are never stored.
-template <bool FULLK, bool SC_CONTIG>
-__device__ __forceinline__ void load_slice(RowSlice& r, const RowSrc& src, int64_t kb0,
-                                           int64_t kbt) {
-    if (FULLK) {
-        const uint4 a = *reinterpret_cast<const uint4*>(src.pay + kb0 * 8);
-        const uint4 b = *reinterpret_cast<const uint4*>(src.pay + kb0 * 8 + 16);
-        r.w[0] = a.x; r.w[1] = a.y; r.w[2] = a.z; r.w[3] = a.w;
-        r.w[4] = b.x; r.w[5] = b.y; r.w[6] = b.z; r.w[7] = b.w;
-        if (SC_CONTIG) {
-            const uint32_t c4 = *reinterpret_cast<const uint32_t*>(src.sc + kb0);
-            r.code[0] = c4;
-            r.code[1] = c4 >> 8;
-            r.code[2] = c4 >> 16;
-            r.code[3] = c4 >> 24;
-        } else {
+__device__ __forceinline__ void load_slice(RowSlice& r, const RowSrc& src, int64_t kb0, int64_t kbt) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) r.code[j] = src.sc[(kb0 + j) * src.sc_stride];
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t kb = kb0 + j < kbt ? kb0 + j : kbt - 1;
-            const uint2 v = *reinterpret_cast<const uint2*>(src.pay + kb * 8);
-            r.w[2 * j] = v.x;
-            r.w[2 * j + 1] = v.y;
-            r.code[j] = src.sc[kb * src.sc_stride];
-        }
+    for (int j = 0; j < 4; ++j) {
+        const int64_t kb = kb0 + j < kbt ? kb0 + j : kbt - 1;
+        const uint2 v = *reinterpret_cast<const uint2*>(src.pay + kb * 8);
+        r.w[2 * j] = v.x;
+        r.w[2 * j + 1] = v.y;
+        r.code[j] = src.sc[kb];
     }
 }
 
-// Decode block j of a slice (16 elements) and store its 16 bf16 to LDS.
-// PACKED: the four scale codes of the slice sit in the bytes of code[0]
-// (one aligned word load); otherwise code[j] holds block j's code.
-template <bool FULLK, bool PACKED>
-__device__ __forceinline__ void store_block(const RowSlice& r, int j, bool v,
-                                            uint16_t* __restrict__ dst) {
-    if (FULLK) v = true;
-    const uint32_t code = PACKED ? (r.code[0] >> (8 * j)) & 0xFFu : r.code[j] & 0xFFu;
-    const uint2 t = scale_factors(v ? code : 0u);
+// Decode block j of a slice (16 elements, zeros unless v) and store its 16
+// fp16 to LDS.
+__device__ __forceinline__ void store_block(const RowSlice& r, int j, bool v, uint16_t* __restrict__ dst) {
+    const uint2 t = scale_factors(v ? r.code[j] & 0xFFu : 0u);
     uint32_t o[8];
     decode8(v ? r.w[2 * j] : 0u, t, o);
     decode8(v ? r.w[2 * j + 1] : 0u, t, o + 4);

@@ -80,7 +80,7 @@ __device__ __forceinline__ void load_frags(Frags& f, const uint16_t* __restrict_
 
 // The 16 MFMAs of one k-step; with DEC, the four decode blocks of one operand
 // row of the next slice (r -> dst) are interleaved with them.
-template <bool FULLK, bool PACKED, bool DEC>
+template <bool DEC>
 __device__ __forceinline__ void kstep(f32x16_t (&acc)[4][4], const Frags& f, int nvalid,
                                       const RowSlice& r, uint16_t* __restrict__ dst) {
 #pragma unroll
@@ -88,7 +88,7 @@ __device__ __forceinline__ void kstep(f32x16_t (&acc)[4][4], const Frags& f, int
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
-        if (DEC) store_block<FULLK, PACKED>(r, i, i < nvalid, dst);
+        if (DEC) store_block(r, i, i < nvalid, dst);
     }
 }
 
@@ -107,7 +107,7 @@ __device__ __forceinline__ void kstep_schedule() {
     }
 }
 
-template <int BMODE, bool OUT_BF16, bool FULLK>
+template <int BMODE, bool OUT_BF16>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_kernel(
     int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n, const uint8_t* __restrict__ A,
     const uint8_t* __restrict__ As, const float* __restrict__ a_dec, const uint8_t* __restrict__ B,
@@ -144,18 +144,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_kernel(
     RowSrc sa, sb;
     sa.pay = A + am * (kbt * 8);
     sa.sc = As + am * kbt;
-    sa.sc_stride = 1;
     sb.pay = B + bn * (kbt * 8);
-    if (BMODE == (int)BScale::Row) {
-        sb.sc = Bs + bn * kbt;
-        sb.sc_stride = 1;
-    } else {
-        sb.sc = Bs + (bn >> 4) * kbt;
-        sb.sc_stride = 1;
-    }
-    constexpr bool kBContig = true;
-    constexpr bool kAPacked = FULLK;
-    constexpr bool kBPacked = FULLK && kBContig;
+    sb.sc = Bs + (BMODE == (int)BScale::Row ? bn : (bn >> 4)) * kbt;
     auto nvalid = [&](int64_t s) -> int { return (int)min((int64_t)4, kbt - s * 4); };
 
     f32x16_t acc[4][4];
@@ -181,16 +171,16 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_kernel(
         // stage nobody reads, which keeps the loop free of branches.
         const int64_t last = (nk - 1) * 4;
         RowSlice ra, rb;
-        load_slice<FULLK, true>(ra, sa, 0, kbt);
-        load_slice<FULLK, kBContig>(rb, sb, 0, kbt);
+        load_slice(ra, sa, 0, kbt);
+        load_slice(rb, sb, 0, kbt);
         const int nv0 = nvalid(0);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            store_block<FULLK, kAPacked>(ra, j, j < nv0, stage0 + tid * LDSK);
-            store_block<FULLK, kBPacked>(rb, j, j < nv0, stage0 + (BM + tid) * LDSK);
+            store_block(ra, j, j < nv0, stage0 + tid * LDSK);
+            store_block(rb, j, j < nv0, stage0 + (BM + tid) * LDSK);
         }
-        load_slice<FULLK, true>(ra, sa, min((int64_t)4, last), kbt);
-        load_slice<FULLK, kBContig>(rb, sb, min((int64_t)4, last), kbt);
+        load_slice(ra, sa, min((int64_t)4, last), kbt);
+        load_slice(rb, sb, min((int64_t)4, last), kbt);
         __syncthreads();
         Frags f0, f1;
         load_frags(f0, stage0, wm, wn, lane, 0);
@@ -200,25 +190,25 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp4_kernel(
             const int nv = nvalid(ks + 1);
             // k-step 0: fragments of k-step 1, MFMAs, decode of the A row
             load_frags(f1, cur, wm, wn, lane, 1);
-            kstep<FULLK, kAPacked, true>(acc, f0, nv, ra, nxt + tid * LDSK);
+            kstep<true>(acc, f0, nv, ra, nxt + tid * LDSK);
             kstep_schedule<8, 0, 6>();
             __builtin_amdgcn_sched_barrier(0);
             // k-step 1: fragments of k-step 2, MFMAs, decode of the B row
             load_frags(f0, cur, wm, wn, lane, 2);
-            kstep<FULLK, kBPacked, true>(acc, f1, nv, rb, nxt + (BM + tid) * LDSK);
+            kstep<true>(acc, f1, nv, rb, nxt + (BM + tid) * LDSK);
             kstep_schedule<8, 0, 6>();
             __builtin_amdgcn_sched_barrier(0);
             // k-step 2: global loads of slice ks+2, fragments of k-step 3
-            load_slice<FULLK, true>(ra, sa, min((ks + 2) * 4, last), kbt);
-            load_slice<FULLK, kBContig>(rb, sb, min((ks + 2) * 4, last), kbt);
+            load_slice(ra, sa, min((ks + 2) * 4, last), kbt);
+            load_slice(rb, sb, min((ks + 2) * 4, last), kbt);
             load_frags(f1, cur, wm, wn, lane, 3);
-            kstep<FULLK, false, false>(acc, f0, nv, ra, nxt);
-            kstep_schedule<8, (FULLK ? (kBContig ? 6 : 9) : 0), 1>();
+            kstep<false>(acc, f0, nv, ra, nxt);
+            kstep_schedule<8, 0, 1>();
             __builtin_amdgcn_sched_barrier(0);
             __syncthreads();
             // k-step 3, overlapping the fragment reads of the next slice
             load_frags(f0, nxt, wm, wn, lane, 0);
-            kstep<FULLK, false, false>(acc, f1, nv, ra, nxt);
+            kstep<false>(acc, f1, nv, ra, nxt);
             kstep_schedule<8, 0, 0>();
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -1609,7 +1599,7 @@ hipError_t launch_mx(int64_t M, int64_t N, int64_t K, const uint8_t* a, const ui
     return hipGetLastError();
 }
 
-template <int BMODE, bool OUT_BF16, bool FULLK>
+template <int BMODE, bool OUT_BF16>
 hipError_t launch_one(int64_t M, int64_t N, int64_t K, const uint8_t* a, const uint8_t* as,
                       const float* ad, const uint8_t* b, const uint8_t* bs, const float* bd,
                       void* c, float amul, hipStream_t s) {
@@ -1621,14 +1611,14 @@ hipError_t launch_one(int64_t M, int64_t N, int64_t K, const uint8_t* a, const u
     if (e != hipSuccess) return e;
     const uint64_t bit = (uint64_t)1 << (dev & 63);
     if ((attr_set.load(std::memory_order_acquire) & bit) == 0) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_fp4_kernel<BMODE, OUT_BF16, FULLK>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_fp4_kernel<BMODE, OUT_BF16>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytes);
         if (e != hipSuccess) return e;
         attr_set.fetch_or(bit, std::memory_order_release);
     }
     const int tiles_m = (int)((M + BM - 1) / BM);
     const int tiles_n = (int)((N + BN - 1) / BN);
-    hipLaunchKernelGGL((gemm_fp4_kernel<BMODE, OUT_BF16, FULLK>),
+    hipLaunchKernelGGL((gemm_fp4_kernel<BMODE, OUT_BF16>),
                        dim3((unsigned)(tiles_m * tiles_n)), dim3(kGemmThreads), kSmemBytes, s, M,
                        N, K, tiles_m, tiles_n, a, as, ad, b, bs, bd, c, amul);
     return hipGetLastError();
@@ -1711,8 +1701,8 @@ hipError_t launch_mode(int cus, int64_t M, int64_t N, int64_t K, const uint8_t* 
     if (K % BK == 0 && K > 0)
         return c_bf16 ? launch_dma<BMODE, true>(M, N, K, a, as, ad, b, bs, bd, c, amul, s)
                       : launch_dma<BMODE, false>(M, N, K, a, as, ad, b, bs, bd, c, amul, s);
-    return c_bf16 ? launch_one<BMODE, true, false>(M, N, K, a, as, ad, b, bs, bd, c, amul, s)
-                  : launch_one<BMODE, false, false>(M, N, K, a, as, ad, b, bs, bd, c, amul, s);
+    return c_bf16 ? launch_one<BMODE, true>(M, N, K, a, as, ad, b, bs, bd, c, amul, s)
+                  : launch_one<BMODE, false>(M, N, K, a, as, ad, b, bs, bd, c, amul, s);
 }
 
 }  // namespace
